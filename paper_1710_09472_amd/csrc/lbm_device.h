@@ -7,10 +7,6 @@
 
 #include <type_traits>
 
-#ifndef LBM_NT_STORE
-#define LBM_NT_STORE 1
-#endif
-
 namespace lbm {
 
 // ---------------------------------------------------------------------------------
@@ -149,26 +145,29 @@ __device__ __forceinline__ void vload(const typename Codec<ST>::T *p, float inv_
     }
 }
 
+// A streamed (non-temporal) store, or with NT = false one that stays in the cache: for
+// stores whose lines a neighbouring wave completes.
+template <bool NT, class VT>
+__device__ __forceinline__ void store_nt(VT v, VT *p)
+{
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
+
 // V encoded values (V-wide store)
-template <int ST, int V>
+template <int ST, int V, bool NT = true>
 __device__ __forceinline__ void vstore_codes(typename Codec<ST>::T *p, const typename Codec<ST>::T *c)
 {
     if constexpr (V == 1) {
-#if LBM_NT_STORE
-        __builtin_nontemporal_store(c[0], p);
-#else
-        *p = c[0];
-#endif
+        store_nt<NT>(c[0], p);
     } else {
         using VT = typename VecT<ST, V>::type;
         VT v;
 #pragma unroll
         for (int i = 0; i < V; ++i) v[i] = c[i];
-#if LBM_NT_STORE
-        __builtin_nontemporal_store(v, reinterpret_cast<VT *>(p));
-#else
-        *reinterpret_cast<VT *>(p) = v;
-#endif
+        store_nt<NT>(v, reinterpret_cast<VT *>(p));
     }
 }
 
@@ -182,22 +181,18 @@ __device__ __forceinline__ void vstore(typename Codec<ST>::T *p, float scale, co
 }
 
 // Population q of V consecutive nodes with node hashes h (values in stored units).
-template <int ST, int V, bool SR>
+template <int ST, int V, bool SR, bool NT = true>
 __device__ __forceinline__ void vstore_q(typename Codec<ST>::T *p, const float *f, const uint32_t *h, int q)
 {
     if constexpr (SR && V == 2 && ST != LBM_F32) {
         using VT = typename VecT<ST, 2>::type;
         const VT v = Codec<ST>::enc_sr2(f[0], sr_bits(h[0], q), f[1], sr_bits(h[1], q));
-#if LBM_NT_STORE
-        __builtin_nontemporal_store(v, reinterpret_cast<VT *>(p));
-#else
-        *reinterpret_cast<VT *>(p) = v;
-#endif
+        store_nt<NT>(v, reinterpret_cast<VT *>(p));
     } else {
         typename Codec<ST>::T c[V];
 #pragma unroll
         for (int i = 0; i < V; ++i) c[i] = enc_store<ST, SR>(f[i], SR ? h[i] : 0u, q);
-        vstore_codes<ST, V>(p, c);
+        vstore_codes<ST, V, NT>(p, c);
     }
 }
 
@@ -744,7 +739,7 @@ __device__ __forceinline__ void collide(const Physics &p, const float *D, float 
 // With SR the codes are rounded stochastically with the node hashes h (sr_node).
 // NT_BOUNCED: the bounced copies are non-temporal stores (the in-place local phase; in the
 // two-buffer step they measured slower: 2048^2 disks +3 %, the paper's 3D Ohm sample +8 %).
-template <int LAT, int ST, bool MASK, int V, bool SR = false, bool NT_BOUNCED = false>
+template <int LAT, int ST, bool MASK, int V, bool SR = false, bool NT_BOUNCED = false, bool NT = true>
 __device__ __forceinline__ void store_tile(const Geometry &g, typename Codec<ST>::T *__restrict__ dst, const Tile &t,
                                            const typename LinkMask<LAT>::T (&lk)[V], const float (&o)[V][Lat<LAT>::Q],
                                            const uint32_t *h = nullptr)
@@ -780,7 +775,7 @@ __device__ __forceinline__ void store_tile(const Geometry &g, typename Codec<ST>
             float f[V];
 #pragma unroll
             for (int i = 0; i < V; ++i) f[i] = o[i][q];
-            vstore_q<ST, V, SR>(p, f, h, q);
+            vstore_q<ST, V, SR, NT>(p, f, h, q);
         } else {
 #pragma unroll
             for (int i = 0; i < V; ++i)

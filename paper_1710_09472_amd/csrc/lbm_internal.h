@@ -193,6 +193,12 @@ hipError_t launch_thermal(int mode, int storage, const ThermalArgs &a, int nbloc
 hipError_t launch_step(int lattice, int storage, int force, const StepArgs &a, hipStream_t st);
 // the same with stochastic rounding (16-bit storage; a.sr set)
 hipError_t launch_step_sr(int lattice, int storage, int force, const StepArgs &a, hipStream_t st);
+// Several D2V9 steps in one launch, two state buffers (lbm_march.hip): `steps` (3 or 5) time
+// steps from a.src into a.dst, the same bits as single steps; keys: the sr_key of each.
+constexpr int kMarchSteps = 5;  // steps per launch at most
+hipError_t launch_march(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st);
+hipError_t launch_march_16(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st);
+hipError_t launch_march_sr(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st);
 // rho <-> mu of the weight (lbm_density.hip); to_mu selects the inverse
 hipError_t launch_density(int D, int stats, double theta, const double *in, double *out, size_t n, bool to_mu,
                           hipStream_t st);

@@ -1,0 +1,74 @@
+"""Several D2V9 steps per launch (strips of a large grid in registers) against single
+steps: lbm_step(n) gives bit for bit the state of n calls of lbm_step(1), in the same state
+buffer, also when the launches are captured and replayed. Sizes at the kernels' edges: widths
+around a strip (56 columns, 224 per block), rows that wrap, grids of few columns or rows,
+remainders of steps."""
+import pytest
+import torch
+
+from paper_1710_09472_amd import lbm
+
+pytestmark = pytest.mark.gpu
+
+# nx, ny (N >= 1310720, the smallest grids of the 16-bit kernels)
+STRIPS = [(56, 24000), (223, 5900), (225, 5861), (1120, 1171), (65537, 21), (350000, 4)]
+
+
+def _sim(nx, ny, storage, rounding, kind, seed=5):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    N = nx * ny
+    rand = lambda: torch.rand(N, device="cuda", generator=g)
+    kw = dict(tau=0.7, storage=storage, dev_scale_log2=12 if storage == "f16" else 0, rounding=rounding)
+    if kind != "open":
+        kw["mask"] = (rand() < 0.15).to(torch.uint8)
+    if kind == "soft":
+        kw["s"] = 0.3 * rand()
+    if kind in ("soft", "slip"):
+        kw |= dict(E=(1e-5, -2e-5, 0.0), B=(0.0, 0.0, 1e-3), forcing="shift" if kind == "slip" else "source")
+    if kind == "slip" and ny >= 3:
+        kw["slip"] = lbm.SLIP_Y
+    if kind == "walls":
+        kw["E"] = (1e-5, 0.0, 0.0)
+    sim = lbm.Simulation("D2V9", nx, ny, 1, **kw)
+    rho = 1.0 + 0.02 * (rand().double() - 0.5)
+    u = 0.02 * torch.stack([rand().double() - 0.5, rand().double() - 0.5])
+    sim.init(rho, u)
+    return sim
+
+
+@pytest.mark.parametrize("kind", ["open", "walls", "soft", "slip"])
+@pytest.mark.parametrize("storage,rounding", [("f32", "nearest"), ("f16", "nearest"), ("bf16", "stochastic")])
+@pytest.mark.parametrize("nx,ny", STRIPS)
+def test_same_bits_as_single_steps(nx, ny, storage, rounding, kind):
+    for steps in (3, 9):
+        one, many = (_sim(nx, ny, storage, rounding, kind) for _ in range(2))
+        for _ in range(steps):
+            one.step(1)
+        many.step(steps)
+        fa = one.export_f64()
+        assert torch.equal(fa, many.export_f64()), steps
+        # the state sits in the buffer that single steps leave it in
+        assert torch.equal(fa, many.export_f64(many.bufs[steps & 1])), steps
+        assert torch.equal(fa, one.export_f64(many.get_state())), steps
+        one.step(1)
+        many.step(1)
+        assert torch.equal(one.export_f64(), many.export_f64()), steps
+
+
+@pytest.mark.parametrize("nx,ny", [(1120, 600)])
+def test_captured_steps_replay(nx, ny):
+    """A graph of an even number of steps advances the state on every replay."""
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        sim, ref = _sim(nx, ny, "f32", "nearest", "walls"), _sim(nx, ny, "f32", "nearest", "walls")
+        sim.step(14)  # warm-up outside the capture
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            sim.step(14)
+        ref.step(14)
+        for _ in range(3):
+            graph.replay()
+            ref.step(14)
+            assert torch.equal(sim.export_f64(), ref.export_f64())
+            torch.cuda.synchronize()
