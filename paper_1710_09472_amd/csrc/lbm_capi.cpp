@@ -49,6 +49,7 @@ struct lbm_s {
     bool adj_held = false;  // work_adj holds adjoint contributions not yet reduced
     bool thermal = false;   // D1V7: the fourth-order thermal model
     ThermalPhysics tph{};
+    TilePlan tile{};        // small D2V9 grids: tiles of the multi-step launches
     std::string err;
 };
 
@@ -297,16 +298,21 @@ int force_level(const lbm_t h)
 // link masks exist where there are solids: obstacles of the mask, or slip wall planes
 bool has_solids(const lbm_t h) { return h->mask != nullptr || h->p.slip != 0; }
 const void *links_of(const lbm_t h) { return has_solids(h) ? h->links : nullptr; }
-// Whether several D2V9 steps go into one launch (k_march, two state buffers): grids on which a
-// launch fills the chip (us per step against single steps: FP32 with solids 900 x 800 8.2
-// (14.9), 512 x 256 7.8 (4.0); FP16 with solids 1280 x 1200 12.9 (16.3), 1024 x 1024 12.8
-// (11.4)). Its reads of bounced links take 32-bit offsets (FP32 with solids: states below
-// 4 GiB).
-bool march_applies(const lbm_t h)
+// How several D2V9 steps go into one launch, on two state buffers. Tiles on small grids, whose
+// single step is a launch and little else; from there on strips in registers, whose one pass
+// over memory serves five steps. The line is where both measured the same (us per step,
+// tiles / strips / single steps): FP32 with solids 1024 x 512 7.0 / 8.1 / 9.4, 900 x 800
+// 10.1 / 8.2 / 14.9; FP16 with solids 1024 x 1024 10.0 / 12.8 / 11.4, 1280 x 1200
+// 14.4 / 12.9 / 16.3. The strips' reads of bounced links take 32-bit offsets (FP32 with
+// solids: states below 4 GiB).
+enum MultiStep { kMultiNone, kMultiTile, kMultiMarch };
+MultiStep multi_step(const lbm_t h)
 {
-    if (h->p.lattice != LBM_D2V9 || h->aa || h->N < (h->p.storage == LBM_F32 ? 655360 : 1310720)) return false;
+    if (h->p.lattice != LBM_D2V9 || h->aa) return kMultiNone;
+    if (h->N < (h->p.storage == LBM_F32 ? 655360 : 1310720)) return kMultiTile;
     const size_t bytes = (size_t)h->Q * (size_t)h->stride * h->elem;
-    return h->p.storage != LBM_F32 || !has_solids(h) || bytes < (1ull << 32);
+    if (h->p.storage == LBM_F32 && has_solids(h) && bytes >= (1ull << 32)) return kMultiNone;
+    return kMultiMarch;
 }
 bool adjoint_supported(const lbm_t h) { return !h->thermal; }
 
@@ -520,6 +526,7 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const float *s, void *s
     h->g.s = s;
     h->g.slip = p->slip;
     h->thermal = p->lattice == LBM_D1V7;
+    if (p->lattice == LBM_D2V9) h->tile = tile_plan(p->nx, p->ny);
     if (h->thermal)
         fill_thermal(h);
     else
@@ -653,13 +660,16 @@ int lbm_step(lbm_t h, int nsteps)
     // that after any number of steps the state is in the buffer single steps would leave it in
     // (a captured sequence of an even number of steps can be replayed).
     int left = nsteps;
-    while (left >= 3 && march_applies(h)) {
-        const int k = left >= kMarchSteps ? kMarchSteps : 3;
-        uint32_t keys[kMarchSteps];
+    const MultiStep multi = multi_step(h);
+    const int most = multi == kMultiTile ? h->tile.steps : kMarchSteps;
+    while (left >= 3 && multi != kMultiNone) {
+        const int k = left >= most ? most : (left - 1) / 2 * 2 + 1;
+        uint32_t keys[kTileSteps];
         for (int i = 0; i < k; ++i) keys[i] = sr_step_key(h->t + (unsigned)i);
         a.src = h->buf[h->cur];
         a.dst = h->buf[h->cur ^ 1];
-        const hipError_t e = launch_march(h->p.storage, force, a, k, keys, h->stream);
+        const hipError_t e = multi == kMultiTile ? launch_tile(h->p.storage, force, a, h->tile, k, keys, h->stream)
+                                                 : launch_march(h->p.storage, force, a, k, keys, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "multi-step kernel launch");
         h->cur ^= 1;
         h->t += (unsigned)k;

@@ -199,6 +199,21 @@ constexpr int kMarchSteps = 5;  // steps per launch at most
 hipError_t launch_march(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st);
 hipError_t launch_march_16(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st);
 hipError_t launch_march_sr(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st);
+// The same on small grids by tiles (lbm_tile.hip): 1 .. p.steps steps in one launch.
+struct TilePlan {
+    int steps;     // most steps per launch (odd), 0: not for this grid
+    int tx, ty;    // nodes a block writes
+    int ntx, nty;  // tiles along x and y
+};
+constexpr int kTileThreads = 1024;  // threads per block at most
+constexpr int kTileSteps = 17;      // steps per launch at most
+TilePlan tile_plan(int nx, int ny);
+hipError_t launch_tile(int storage, int force, const StepArgs &a, const TilePlan &p, int steps, const uint32_t *keys,
+                       hipStream_t st);
+hipError_t launch_tile_16(int storage, int force, const StepArgs &a, const TilePlan &p, int steps,
+                          const uint32_t *keys, hipStream_t st);
+hipError_t launch_tile_sr(int storage, int force, const StepArgs &a, const TilePlan &p, int steps,
+                          const uint32_t *keys, hipStream_t st);
 // rho <-> mu of the weight (lbm_density.hip); to_mu selects the inverse
 hipError_t launch_density(int D, int stats, double theta, const double *in, double *out, size_t n, bool to_mu,
                           hipStream_t st);

@@ -1,8 +1,8 @@
-"""Several D2V9 steps per launch (strips of a large grid in registers) against single
+"""Several D2V9 steps per launch (tiles on small grids, strips on large ones) against single
 steps: lbm_step(n) gives bit for bit the state of n calls of lbm_step(1), in the same state
 buffer, also when the launches are captured and replayed. Sizes at the kernels' edges: widths
-around a strip (56 columns, 224 per block), rows that wrap, grids of few columns or rows,
-remainders of steps."""
+around a strip (56 columns, 224 per block) and a tile, rows that wrap, grids narrower or
+shorter than a tile, remainders of steps, on both sides of the line between the kernels."""
 import pytest
 import torch
 
@@ -10,7 +10,8 @@ from paper_1710_09472_amd import lbm
 
 pytestmark = pytest.mark.gpu
 
-# nx, ny (N >= 1310720, the smallest grids of the 16-bit kernels)
+# nx, ny: tiles (one block, ragged tiles, thin grids), strips (N >= 655360 in FP32, >= 1310720 in 16 bits)
+TILES = [(1, 1), (5, 3), (16, 16), (33, 18), (70, 9), (300, 5), (4, 131), (301, 290), (1000, 640)]
 STRIPS = [(56, 24000), (223, 5900), (225, 5861), (1120, 1171), (65537, 21), (350000, 4)]
 
 
@@ -38,9 +39,9 @@ def _sim(nx, ny, storage, rounding, kind, seed=5):
 
 @pytest.mark.parametrize("kind", ["open", "walls", "soft", "slip"])
 @pytest.mark.parametrize("storage,rounding", [("f32", "nearest"), ("f16", "nearest"), ("bf16", "stochastic")])
-@pytest.mark.parametrize("nx,ny", STRIPS)
+@pytest.mark.parametrize("nx,ny", TILES + STRIPS)
 def test_same_bits_as_single_steps(nx, ny, storage, rounding, kind):
-    for steps in (3, 9):
+    for steps in (4, 23) if nx * ny < 655360 else (3, 9):
         one, many = (_sim(nx, ny, storage, rounding, kind) for _ in range(2))
         for _ in range(steps):
             one.step(1)
@@ -55,7 +56,7 @@ def test_same_bits_as_single_steps(nx, ny, storage, rounding, kind):
         assert torch.equal(one.export_f64(), many.export_f64()), steps
 
 
-@pytest.mark.parametrize("nx,ny", [(1120, 600)])
+@pytest.mark.parametrize("nx,ny", [(300, 290), (1120, 600)])
 def test_captured_steps_replay(nx, ny):
     """A graph of an even number of steps advances the state on every replay."""
     stream = torch.cuda.Stream()
