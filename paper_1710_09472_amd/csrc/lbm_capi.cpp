@@ -633,14 +633,18 @@ int lbm_step(lbm_t h, int nsteps)
         return LBM_OK;
     }
     if (h->thermal) {
+        // an odd number of steps per launch, as for the other lattices below
         ThermalArgs ta = thermal_args(h);
-        for (int t = 0; t < nsteps; ++t) {
+        for (int left = nsteps; left > 0;) {
+            const int k = left >= kThermalSteps ? kThermalSteps : (left - 1) / 2 * 2 + 1;
             ta.src = h->buf[h->cur];
             ta.dst = h->buf[h->cur ^ 1];
-            const hipError_t e = launch_thermal(0, h->p.storage, ta, 0, h->stream);
+            const hipError_t e = k == 1 ? launch_thermal(0, h->p.storage, ta, 0, h->stream)
+                                        : launch_thermal_multi(h->p.storage, ta, k, h->stream);
             if (e != hipSuccess) return hip_fail(h, e, "thermal step kernel launch");
             h->cur ^= 1;
-            ++h->t;
+            h->t += (unsigned)k;
+            left -= k;
         }
         return LBM_OK;
     }

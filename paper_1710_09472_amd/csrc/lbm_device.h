@@ -260,6 +260,16 @@ __device__ __forceinline__ void for_q(F &&f)
     }
 }
 
+// Value of the previous / next lane of the wave (lanes 0 and 63 get an unused value).
+__device__ __forceinline__ float lane_prev(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float lane_next(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xF, 0xF, true));
+}
+
 template <int LAT>
 struct LinkMask;
 template <>

@@ -188,6 +188,10 @@ struct ThermalArgs {
 // 5, 6: the two phases of the in-place step (src == dst); 7: odd layout src -> even dst
 hipError_t launch_thermal(int mode, int storage, const ThermalArgs &a, int nblocks_reduce, hipStream_t st);
 
+// `steps` (1 .. kThermalSteps) steps src -> dst in one launch, the same bits as single steps
+constexpr int kThermalSteps = 5;
+hipError_t launch_thermal_multi(int storage, const ThermalArgs &a, int steps, hipStream_t st);
+
 // Launchers (lbm_kernels.hip). Each returns hipSuccess or the launch error.
 // force: 0 no field, 1 E only, 2 E and B.
 hipError_t launch_step(int lattice, int storage, int force, const StepArgs &a, hipStream_t st);

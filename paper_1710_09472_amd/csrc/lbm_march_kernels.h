@@ -42,16 +42,6 @@ constexpr int kMarchBlock = 256;  // threads per block: four strips side by side
 constexpr int kMarchHalo = kMarchSteps - 1;          // lanes on each side that only feed their neighbours
 constexpr int kMarchWidth = 64 - 2 * kMarchHalo;     // columns a wave writes
 
-// Value of the previous / next lane of the wave (lanes 0 and 63 get an unused value).
-__device__ __forceinline__ float lane_prev(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xF, 0xF, true));
-}
-__device__ __forceinline__ float lane_next(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xF, 0xF, true));
-}
-
 // a where bit q of the link mask is set, else b: the bit spread over a word selects bitwise,
 // two instructions (the compiler's own choice, and + compare + select, is three).
 template <int q>

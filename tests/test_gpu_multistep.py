@@ -73,3 +73,26 @@ def test_captured_steps_replay(nx, ny):
             ref.step(14)
             assert torch.equal(sim.export_f64(), ref.export_f64())
             torch.cuda.synchronize()
+
+
+def _thermal(n, storage, order):
+    g = torch.Generator(device="cuda").manual_seed(7)
+    noise = lambda: 0.01 * (torch.rand(n, device="cuda", generator=g).double() - 0.5)
+    sim = lbm.Simulation("D1V7", n, 1, 1, tau=0.8, theta=0.25, mu=1.0, storage=storage, order=order,
+                         dev_scale_log2=17 if storage == "f16" else 0)
+    k = lbm.compute_constants("D1V7", "fd", 0.25, 1.0)
+    sim.init(1.0 + noise(), noise(), k["I2"] / k["I0"] * (1.0 + noise()))
+    return sim
+
+
+@pytest.mark.parametrize("storage,order", [("f32", 4), ("f16", 4), ("bf16", 3)])
+@pytest.mark.parametrize("n", [1, 2, 7, 63, 479, 480, 481, 511, 513, 1920, 1923, 70001])
+def test_thermal_same_bits_as_single_steps(n, storage, order):
+    for steps in (3, 4, 23):
+        one, many = _thermal(n, storage, order), _thermal(n, storage, order)
+        for _ in range(steps):
+            one.step(1)
+        many.step(steps)
+        fa = one.export_f64()
+        assert torch.equal(fa, many.export_f64()), steps
+        assert torch.equal(fa, many.export_f64(many.bufs[steps & 1])), steps
