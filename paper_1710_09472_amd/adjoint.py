@@ -69,7 +69,7 @@ def forward_with_checkpoints(pb: Problem, E, tau, s):
     sim = _make_sim(pb, E, tau, s)
     sim.init(pb.rho, pb.u)
     if pb.keep_states:
-        states = [sim.get_state()]
+        states = [sim.get_state(sim.new_state(zero=False))]
         sim.set_step_index(0)
         for _ in range(pb.steps):
             nxt = sim.new_state(zero=False)  # written by the step where any pull reads
@@ -80,7 +80,7 @@ def forward_with_checkpoints(pb: Problem, E, tau, s):
         return tot[1 + pb.axis] / pb.N, sim, states
     cps = []
     for t0 in range(0, pb.steps, pb.checkpoint):
-        cps.append(sim.get_state())
+        cps.append(sim.get_state(sim.new_state(zero=False)))
         sim.step(min(pb.checkpoint, pb.steps - t0))
     tot = sim.current()
     return tot[1 + pb.axis] / pb.N, sim, cps
@@ -100,18 +100,19 @@ def adjoint_gradients(pb: Problem, sim: Simulation, cps):
             sim.adjoint_step(cps[t], lam[cur], lam[cur ^ 1], gs, gsc if t == 0 else None)
             cur ^= 1
         return gsc[:3].clone(), gsc[3].clone(), gs, lam[cur]
-    seg_bufs = [sim.new_state() for _ in range(K)]
+    # the states of one segment after its checkpoint (each written as a whole by its step)
+    seg_bufs = [sim.new_state(zero=False) for _ in range(min(K, pb.steps) - 1)]
     nseg = len(cps)
     for i in range(nseg - 1, -1, -1):
         t0 = i * K
         n = min(K, pb.steps - t0)
-        seg_bufs[0].copy_(cps[i])
+        seg = [cps[i]] + seg_bufs[: n - 1]
         sim.set_step_index(t0)  # the recomputed steps repeat the forward run's bits
         for k in range(1, n):
-            sim.step_from(seg_bufs[k - 1], seg_bufs[k])
+            sim.step_from(seg[k - 1], seg[k])
         for k in range(n - 1, -1, -1):
             # dJ/dE, dJ/dtau stay as per-block partials until the last step of the pass
-            sim.adjoint_step(seg_bufs[k], lam[cur], lam[cur ^ 1], gs, gsc if (i == 0 and k == 0) else None)
+            sim.adjoint_step(seg[k], lam[cur], lam[cur ^ 1], gs, gsc if (i == 0 and k == 0) else None)
             cur ^= 1
     return gsc[:3].clone(), gsc[3].clone(), gs, lam[cur]
 

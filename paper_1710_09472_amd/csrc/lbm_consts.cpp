@@ -75,26 +75,35 @@ int weight_integrals_n(int stats, int D, double theta, double mu, int n, double 
     if (stats != LBM_FERMI_DIRAC && stats != LBM_BOSE_EINSTEIN) return LBM_EINVAL;
     if (!(theta > 0) || !std::isfinite(theta) || !std::isfinite(mu)) return LBM_EINVAL;
     if (stats == LBM_BOSE_EINSTEIN && !(mu < 0)) return LBM_EINVAL;
-    // The integrand is negligible beyond xi^2 = mu + 80 theta (omega < e^-80). Panels
-    // are narrower than the width of the Fermi edge (~theta/2 in xi near xi^2 = mu), or,
-    // for the Bose-Einstein weight, than a quarter of its scales sqrt(theta) and
-    // sqrt(|mu|); nodes, weights and sums are carried in long double and rounded once.
+    // The integrand is negligible beyond xi^2 = mu + 80 theta (omega < e^-80). Where
+    // xi^2 < mu - 50 theta, the Fermi-Dirac weight is 1 to within e^-50 and the integrand a
+    // polynomial of degree <= 10, which one panel of 10 points integrates exactly. The rest
+    // goes in panels of half-width r <= d / 8, d the distance of the weight's nearest pole from
+    // the real axis (xi^2 = mu + i pi theta, or mu itself for the Bose-Einstein weight): the
+    // error of 10 points falls as (d/r + sqrt((d/r)^2 + 1))^-20 < 1e-24 of the integrand; and
+    // r <= theta / (4 xmax), so that the exponent changes by less than 1 over a panel. Nodes,
+    // weights and sums are carried in long double and rounded once. (The electron weight:
+    // 170 panels, 0.2 ms of host time for each handle; a uniform grid of 1400 took 1.7 ms.)
     const long double th = theta, m = mu;
     const long double xmax = std::sqrt(std::fmax(mu, 0.0) + 80.0 * theta);
-    const long double h = stats == LBM_FERMI_DIRAC
-                              ? std::fmin(1e-3L, 0.25L * th / std::fmax(1.0L, xmax))
-                              : std::fmin(1e-3L, 0.25L * std::sqrt(std::fmin(th, std::fabs(m))));
-    const int npan = (int)std::ceil(xmax / h);
+    long double flat = 0.0L, d = std::sqrt(std::fabs(m));
+    if (stats == LBM_FERMI_DIRAC) {
+        flat = std::sqrt(std::fmax(m - 50.0L * th, 0.0L));
+        d = std::sqrt(std::complex<long double>(m, (long double)M_PI * th)).imag();
+    }
+    const long double h = std::fmin(d / 4.0L, 0.5L * th / xmax);
+    const int npan = (int)std::ceil((xmax - flat) / h);
     std::vector<long double> gx, gw;
     gauss_legendre(10, gx, gw);
     long double acc[5] = {0, 0, 0, 0, 0};
-    for (int p = 0; p < npan; ++p) {
-        const long double a = p * (xmax / npan), b = (p + 1) * (xmax / npan);
+    for (int p = flat > 0 ? -1 : 0; p < npan; ++p) {
+        const long double a = p < 0 ? 0.0L : flat + p * ((xmax - flat) / npan);
+        const long double b = p < 0 ? flat : flat + (p + 1) * ((xmax - flat) / npan);
         const long double c = 0.5L * (a + b), r = 0.5L * (b - a);
         for (size_t k = 0; k < gx.size(); ++k) {
             const long double xi = c + r * gx[k];
             const long double wk = r * gw[k] * omega(stats, xi, th, m, D);
-            long double pw = D == 1 ? 1.0L : std::pow(xi, (long double)(D - 1));
+            long double pw = D == 1 ? 1.0L : (D == 2 ? xi : xi * xi);
             for (int N = 0; N < n; ++N) {
                 acc[N] += wk * pw;
                 pw *= xi * xi;
