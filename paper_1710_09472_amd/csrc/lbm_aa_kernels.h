@@ -325,9 +325,19 @@ hipError_t aa_v(int force, int phase, const StepArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
+// The local phase without solids reads and writes every node at its own slots and nowhere
+// else, so its tiles need not follow the rows: as one row of N nodes every block starts on a
+// cache line whatever nx is. (Measured on MI355X, BF16 4000 x 3001, where every second row
+// starts in mid-line: 108.5 us per phase by rows, 63.9 us as one row.)
 template <int LAT, int ST, bool SR>
-hipError_t aa_lat_st(int force, int phase, const StepArgs &a, hipStream_t st)
+hipError_t aa_lat_st(int force, int phase, const StepArgs &a0, hipStream_t st)
 {
+    StepArgs a = a0;
+    if (phase == 1 && !a.links) {
+        a.g.nx = a.g.nx * a.g.ny * a.g.nz;
+        a.g.ny = a.g.nz = 1;
+        a.g.div_ny = make_fastdiv(1);
+    }
     if (step_vector_width(LAT, ST, a.g.nx, a.links != nullptr && phase == 1) == 2)
         return aa_v<LAT, ST, 2, SR>(force, phase, a, st);
     return aa_v<LAT, ST, 1, SR>(force, phase, a, st);
