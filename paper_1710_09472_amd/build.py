@@ -2,7 +2,7 @@
 
 Sources: ``csrc/lbm_kernels.hip`` (device kernels and launchers; device helpers in
 ``csrc/lbm_device.h``), ``csrc/lbm_march*.hip`` and ``csrc/lbm_tile*.hip`` (several D2V9
-steps per launch), ``csrc/lbm_aa.hip`` (the in-place step), ``csrc/lbm_thermal.hip``
+steps per launch), ``csrc/lbm_march3*.hip`` (two D3V19 steps per launch), ``csrc/lbm_aa.hip`` (the in-place step), ``csrc/lbm_thermal.hip``
 (the fourth-order thermal model on D1V7), ``csrc/lbm_density.hip``
 (rho <-> mu), ``csrc/lbm_capi.cpp`` (the C ABI of ``include/lbm.h``) and
 ``csrc/lbm_consts.cpp`` (host FP64 constants).
@@ -23,7 +23,8 @@ CSRC = PKG / "csrc"
 INCLUDE = ROOT / "include"
 BUILD = PKG / "_build"
 LIB = PKG / "liblbm_hip.so"
-SOURCES = ["lbm_kernels.hip", "lbm_aa.hip", "lbm_step_sr.hip", "lbm_aa_sr.hip", "lbm_march.hip", "lbm_march_16.hip", "lbm_march_sr.hip", "lbm_tile.hip", "lbm_tile_16.hip", "lbm_tile_sr.hip", "lbm_thermal.hip", "lbm_density.hip", "lbm_capi.cpp", "lbm_consts.cpp"]
+SOURCES = ["lbm_kernels.hip", "lbm_aa.hip", "lbm_step_sr.hip", "lbm_aa_sr.hip", "lbm_march.hip", "lbm_march_16.hip", "lbm_march_sr.hip", "lbm_march3.hip", "lbm_march3_f16.hip", "lbm_march3_f16_sr.hip", "lbm_march3_bf16.hip",
+           "lbm_march3_bf16_sr.hip", "lbm_tile.hip", "lbm_tile_16.hip", "lbm_tile_sr.hip", "lbm_thermal.hip", "lbm_density.hip", "lbm_capi.cpp", "lbm_consts.cpp"]
 ARCH = os.environ.get("LBM_OFFLOAD_ARCH", "gfx950")
 
 

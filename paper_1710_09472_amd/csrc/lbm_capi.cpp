@@ -298,20 +298,29 @@ int force_level(const lbm_t h)
 // link masks exist where there are solids: obstacles of the mask, or slip wall planes
 bool has_solids(const lbm_t h) { return h->mask != nullptr || h->p.slip != 0; }
 const void *links_of(const lbm_t h) { return has_solids(h) ? h->links : nullptr; }
-// How several D2V9 steps go into one launch, on two state buffers. Tiles on small grids, whose
+// How several steps go into one launch, on two state buffers. D2V9: tiles on small grids, whose
 // single step is a launch and little else; from there on strips in registers, whose one pass
 // over memory serves five steps. The line is where both measured the same (us per step,
 // tiles / strips / single steps): FP32 with solids 1024 x 512 7.0 / 8.1 / 9.4, 900 x 800
 // 10.1 / 8.2 / 14.9; FP16 with solids 1024 x 1024 10.0 / 12.8 / 11.4, 1280 x 1200
-// 14.4 / 12.9 / 16.3. The strips' reads of bounced links take 32-bit offsets (FP32 with
-// solids: states below 4 GiB).
-enum MultiStep { kMultiNone, kMultiTile, kMultiMarch };
+// 14.4 / 12.9 / 16.3. D3V19: blocks marching along z, two steps per launch, where the grid
+// fills them (us per step, two / one per launch: FP32 128 x 64 x 64 14.1 / 15.9, 64^3
+// 17.6 / 11.6) and memory, not the VALU, bounds the single step: 16-bit states that stay in
+// the 256 MB Infinity Cache do not gain with solids or stochastic rounding (FP16 duct
+// 256 x 128 x 128 61.4 / 58.5, 256^3 duct 222 / 249; FP16 128^3 periodic 28.0 / 32.4). The
+// reads of bounced links take 32-bit offsets (FP32 with solids: states below 4 GiB).
+enum MultiStep { kMultiNone, kMultiTile, kMultiMarch, kMultiMarch3 };
 MultiStep multi_step(const lbm_t h)
 {
-    if (h->p.lattice != LBM_D2V9 || h->aa) return kMultiNone;
-    if (h->N < (h->p.storage == LBM_F32 ? 655360 : 1310720)) return kMultiTile;
+    if (h->aa) return kMultiNone;
     const size_t bytes = (size_t)h->Q * (size_t)h->stride * h->elem;
     if (h->p.storage == LBM_F32 && has_solids(h) && bytes >= (1ull << 32)) return kMultiNone;
+    if (h->p.lattice == LBM_D3V19) {
+        const bool plain = !has_solids(h) && h->p.rounding == LBM_ROUND_NEAREST;
+        return h->N >= (h->p.storage == LBM_F32 ? 500000 : (plain ? 2000000 : 8000000)) ? kMultiMarch3 : kMultiNone;
+    }
+    if (h->p.lattice != LBM_D2V9) return kMultiNone;
+    if (h->N < (h->p.storage == LBM_F32 ? 655360 : 1310720)) return kMultiTile;
     return kMultiMarch;
 }
 bool adjoint_supported(const lbm_t h) { return !h->thermal; }
@@ -666,7 +675,20 @@ int lbm_step(lbm_t h, int nsteps)
     int left = nsteps;
     const MultiStep multi = multi_step(h);
     const int most = multi == kMultiTile ? h->tile.steps : kMarchSteps;
-    while (left >= 3 && multi != kMultiNone) {
+    // D3V19: two steps per launch, an even number of launches
+    while (left >= 4 && multi == kMultiMarch3) {
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t keys[2] = {sr_step_key(h->t), sr_step_key(h->t + 1)};
+            a.src = h->buf[h->cur];
+            a.dst = h->buf[h->cur ^ 1];
+            const hipError_t e = launch_march3(h->p.storage, force, a, keys, h->stream);
+            if (e != hipSuccess) return hip_fail(h, e, "multi-step kernel launch");
+            h->cur ^= 1;
+            h->t += 2;
+            left -= 2;
+        }
+    }
+    while (left >= 3 && (multi == kMultiTile || multi == kMultiMarch)) {
         const int k = left >= most ? most : (left - 1) / 2 * 2 + 1;
         uint32_t keys[kTileSteps];
         for (int i = 0; i < k; ++i) keys[i] = sr_step_key(h->t + (unsigned)i);

@@ -270,6 +270,18 @@ __device__ __forceinline__ float lane_next(float v)
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xF, 0xF, true));
 }
 
+// a where bit q of the link mask is set, else b: the bit spread over a word selects bitwise,
+// two instructions (the compiler's own choice, and + compare + select, is three).
+template <int q>
+__device__ __forceinline__ float link_select(unsigned lk, float a, float b)
+{
+    unsigned m;
+    float r;
+    asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m) : "v"(lk), "n"(q));
+    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(m), "v"(a), "v"(b));
+    return r;
+}
+
 template <int LAT>
 struct LinkMask;
 template <>
@@ -659,6 +671,15 @@ __device__ __forceinline__ Macro<LAT> macro(const Physics &p, const float *d)
 // sigma_q = (e_q.c1v) + c2q (e_q.U) + C2_k c_s (U.E) + C2_k e_q.(U x B). The rest population
 // follows from mass closure (relaxation and source conserve mass), o_0 = sum_q D_q -
 // sum_{q>0} o_q, which also keeps FP32 mass conservation exact up to one rounding per node.
+// The force constants are odd in e_q: one scalar register serves a pair of opposite
+// populations (half of the 2 x 18 of D3V19, which otherwise spill to vector lanes).
+template <int LAT, int q>
+__device__ __forceinline__ float odd_const(const float *c)
+{
+    constexpr int p = Lat<LAT>::opp[q];
+    return q < p ? c[q] : -c[p];
+}
+
 template <int LAT, int FORCE>
 __device__ __forceinline__ void relax_node(const Physics &p, const float *D, float *o)
 {
@@ -713,9 +734,9 @@ __device__ __forceinline__ void relax_node(const Physics &p, const float *D, flo
             if constexpr (FORCE == 0 || FORCE == 3)
                 inner = __builtin_fmaf(p.omBc * eu, eu, P[k]);
             else if constexpr (FORCE == 1)
-                inner = __builtin_fmaf(__builtin_fmaf(p.omBc, eu, p.c2q[q]), eu, P[k] + p.c1q[q]);
+                inner = __builtin_fmaf(__builtin_fmaf(p.omBc, eu, odd_const<LAT, q>(p.c2q)), eu, P[k] + odd_const<LAT, q>(p.c1q));
             else
-                inner = __builtin_fmaf(__builtin_fmaf(p.omBc, eu, p.c2q[q]), eu, P[k] + edot<LAT, q>(H[k]));
+                inner = __builtin_fmaf(__builtin_fmaf(p.omBc, eu, odd_const<LAT, q>(p.c2q)), eu, P[k] + edot<LAT, q>(H[k]));
             const float v = __builtin_fmaf(wr[k], inner,
                                            __builtin_fmaf(p.ol[k], ej, __builtin_fmaf(p.c0, D[q], owd[k])));
             o[q] = v;

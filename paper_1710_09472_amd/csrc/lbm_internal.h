@@ -203,6 +203,12 @@ constexpr int kMarchSteps = 5;  // steps per launch at most
 hipError_t launch_march(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st);
 hipError_t launch_march_16(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st);
 hipError_t launch_march_sr(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st);
+// Two D3V19 steps in one launch, two state buffers (lbm_march3.hip), the same bits as single steps.
+hipError_t launch_march3(int storage, int force, const StepArgs &a, const uint32_t *keys, hipStream_t st);
+hipError_t launch_march3_f16(int force, const StepArgs &a, const uint32_t *keys, hipStream_t st);
+hipError_t launch_march3_f16_sr(int force, const StepArgs &a, const uint32_t *keys, hipStream_t st);
+hipError_t launch_march3_bf16(int force, const StepArgs &a, const uint32_t *keys, hipStream_t st);
+hipError_t launch_march3_bf16_sr(int force, const StepArgs &a, const uint32_t *keys, hipStream_t st);
 // The same on small grids by tiles (lbm_tile.hip): 1 .. p.steps steps in one launch.
 struct TilePlan {
     int steps;     // most steps per launch (odd), 0: not for this grid

@@ -1,0 +1,12 @@
+// lbm_march3_bf16_sr.hip -- two D3V19 time steps per launch (lbm_march3_kernels.h), BF16 storage
+// with stochastic rounding.
+#include "lbm_march3_kernels.h"
+
+namespace lbm {
+
+hipError_t launch_march3_bf16_sr(int force, const StepArgs &a, const uint32_t *keys, hipStream_t st)
+{
+    return march3_st<LBM_BF16, true>(force, a, keys, st);
+}
+
+}  // namespace lbm

@@ -1,0 +1,13 @@
+// lbm_march3_f16.hip -- two D3V19 time steps per launch (lbm_march3_kernels.h), F16 storage
+// rounded to nearest.
+#include "lbm_march3_kernels.h"
+
+namespace lbm {
+
+hipError_t launch_march3_f16(int force, const StepArgs &a, const uint32_t *keys, hipStream_t st)
+{
+    if (a.sr) return launch_march3_f16_sr(force, a, keys, st);
+    return march3_st<LBM_F16, false>(force, a, keys, st);
+}
+
+}  // namespace lbm

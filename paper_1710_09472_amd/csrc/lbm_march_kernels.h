@@ -42,18 +42,6 @@ constexpr int kMarchBlock = 256;  // threads per block: four strips side by side
 constexpr int kMarchHalo = kMarchSteps - 1;          // lanes on each side that only feed their neighbours
 constexpr int kMarchWidth = 64 - 2 * kMarchHalo;     // columns a wave writes
 
-// a where bit q of the link mask is set, else b: the bit spread over a word selects bitwise,
-// two instructions (the compiler's own choice, and + compare + select, is three).
-template <int q>
-__device__ __forceinline__ float link_select(unsigned lk, float a, float b)
-{
-    unsigned m;
-    float r;
-    asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m) : "v"(lk), "n"(q));
-    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(m), "v"(a), "v"(b));
-    return r;
-}
-
 // What a later step of a launch keeps between two rows, r being the row of the step before
 // it that came last.
 struct Carry {
