@@ -211,6 +211,15 @@ __device__ __forceinline__ T *at32(T *base, unsigned idx)
     return reinterpret_cast<T *>(reinterpret_cast<C *>(base) + idx * (unsigned)sizeof(T));
 }
 
+// A loop-invariant lane offset, made opaque inside the loop: otherwise its extension to 64
+// bits is hoisted out, and every access adds the row's base per lane (a 64-bit VALU add)
+// instead of taking it as a scalar.
+__device__ __forceinline__ unsigned lane_offset(unsigned x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
 // ---------------------------------------------------------------------------------
 // Lattice helpers (all indices compile-time after unrolling).
 // ---------------------------------------------------------------------------------

@@ -108,10 +108,11 @@ __global__ __launch_bounds__(kM3Threads, 4) void k_march3(March3Args ma)
             t.y = y;
             r.ym = wrapm(y, ny);
             r.yp = wrapp(y, ny);
+            const unsigned xc = lane_offset(x), xl = lane_offset(r.xl), xr = lane_offset(r.xr);
             for_q<L::Q>([&](auto qc) {
                 constexpr int q = decltype(qc)::value;
                 const size_t off = pull_row<LAT, q>(g, t, r);
-                const unsigned xq = L::ex[q] > 0 ? r.xl : (L::ex[q] < 0 ? r.xr : x);
+                const unsigned xq = L::ex[q] > 0 ? xl : (L::ex[q] < 0 ? xr : xc);
                 if constexpr (sel.value && q != 0) {
                     const unsigned own = (unsigned)L::opp[q] * (unsigned)g.stride + x + (unsigned)nx * (unsigned)(y + ny * z);
                     c[q] = *at32(src, (lk >> q) & 1u ? own : (unsigned)off + xq);
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(kM3Threads, 4) void k_march3(March3Args ma)
                 t.x0 = xi;
                 t.y = ys;
                 t.z = z0 + it - 2;
-                t.own = xi + nx * (ys + ny * t.z);
+                t.own = (int)lane_offset((unsigned)(xi + nx * (ys + ny * t.z)));
                 t.valid = true;
                 const LT lo[1] = {(LT)lk2};
                 const uint32_t h[1] = {SR ? sr_node((uint32_t)t.own, ma.key[1]) : 0u};

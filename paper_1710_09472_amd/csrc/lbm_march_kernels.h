@@ -115,10 +115,14 @@ __global__ __launch_bounds__(kMarchBlock, 4) void k_march(MarchArgs ma)
     // that no load waits for another (32-bit offsets: the state is below 4 GiB there).
     auto load_row = [&](int y, LT lk, Row &row) {
         to_row(y);
+        // (with a mask, FP32 1531 x 1117 disks: 12.0 -> 11.8 us per step with the unrolling below;
+        // without one the widened offsets cost nothing and pinning them cost 1-2 %)
+        const unsigned xc = MASK ? lane_offset(x) : x;
+        const unsigned xl = MASK ? lane_offset(r.xl) : r.xl, xr = MASK ? lane_offset(r.xr) : r.xr;
         for_q<L::Q>([&](auto qc) {
             constexpr int q = decltype(qc)::value;
             const size_t off = pull_row<LAT, q>(g, t, r);
-            const unsigned xq = L::ex[q] > 0 ? r.xl : (L::ex[q] < 0 ? r.xr : x);
+            const unsigned xq = L::ex[q] > 0 ? xl : (L::ex[q] < 0 ? xr : xc);
             if constexpr (MASK && !kSolidSlotBB<ST> && q != 0) {
                 const unsigned own = (unsigned)L::opp[q] * (unsigned)g.stride + (unsigned)t.own;
                 row.c[q] = *at32(src, (lk >> q) & 1u ? own : (unsigned)off + xq);
@@ -201,9 +205,9 @@ __global__ __launch_bounds__(kMarchBlock, 4) void k_march(MarchArgs ma)
     if (y < 0) y += ny;
     const int first = 2 * (steps - 1), nit = nrows + first;
     LT lk0 = load_lk(y), lk1 = load_lk(wrapp(y, ny));
-    Row cur, nxt;
-    load_row(y, lk0, cur);
-    for (int it = 0; it < nit; ++it) {
+    Row row0, row1;
+    load_row(y, lk0, row0);
+    auto iteration = [&](int it, Row &cur, Row &nxt) {
         const int yn = wrapp(y, ny);
         load_row(yn, lk1, nxt);  // (past the segment's end: rows of the grid all the same)
         LT lk2 = load_lk(wrapp(yn, ny));
@@ -229,15 +233,28 @@ __global__ __launch_bounds__(kMarchBlock, 4) void k_march(MarchArgs ma)
         if (MASK) asm volatile("" : "+v"(lk2));
         if (it >= first && writes) {
             to_row(y0 + it - first);
+            if (MASK) t.own = (int)lane_offset((unsigned)t.own);
             const LT lo[1] = {(LT)lk};
             float(&o1)[1][L::Q] = reinterpret_cast<float(&)[1][L::Q]>(o);
             const uint32_t h[1] = {SR ? sr_node((uint32_t)t.own, ma.last_key) : 0u};
             store_tile<LAT, ST, MASK, 1, SR, false, false>(g, static_cast<T *>(a.dst), t, lo, o1, h);
         }
         y = yn;
-        cur = nxt;
         lk0 = lk1;
         lk1 = lk2;
+    };
+    if constexpr (MASK) {
+        // two at a time, so that the row buffers change roles without moves (without a mask that
+        // costs registers and with them a block per CU: FP32 4096^2, 50 steps 3.71 -> 3.82 ms)
+        for (int it = 0; it < nit; it += 2) {
+            iteration(it, row0, row1);
+            if (it + 1 < nit) iteration(it + 1, row1, row0);
+        }
+    } else {
+        for (int it = 0; it < nit; ++it) {
+            iteration(it, row0, row1);
+            row0 = row1;
+        }
     }
 }
 
