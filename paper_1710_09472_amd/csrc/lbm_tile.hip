@@ -6,27 +6,34 @@
 
 namespace lbm {
 
-// Tiles by measurement (us per step, FP32 with solids): 16 x 16 with 9 steps where such tiles
-// fit the 256 CUs once (64 x 32: 1.36, 256 x 256: 1.60; 32 x 16 with 5 steps: 1.7, 2.1),
-// 32 x 16 with 5 steps where they do not (300 x 300: 2.4 against 2.9; 512 x 256: 2.5 against
-// 2.8). Grids of few rows (columns): the tile spans them, so that only the long axis has a
-// halo and more steps fit (4096 x 4, 17 steps on 32 columns: 0.7).
+// Tiles by measurement: the most steps whose tiles still fit the 256 CUs about once (a second
+// block per CU takes turns with the first), on the smallest tiles that do (fewer wavefronts
+// per SIMD). us per step, FP32 with solids:
+//   64 x 32    4 x 4, 9 steps 0.75    8 x 8, 9 steps 0.86    16 x 16, 9 steps 1.04
+//   128 x 128  8 x 8, 9 steps 0.94    16 x 16, 9 steps 1.06  8 x 8, 5 steps 1.03
+//   256 x 256  16 x 16, 9 steps 1.36  16 x 16, 5 steps 1.67  16 x 8, 9 steps 1.48
+//   300 x 290  20 x 18, 7 steps 1.87  16 x 16, 9 steps 1.96  32 x 16, 5 steps 1.99
+//   512 x 256  32 x 16, 5 steps 2.19  20 x 12, 7 steps 2.29  32 x 16, 3 steps 2.91
+//   512 x 512  24 x 24, 5 steps 2.91  32 x 16, 5 steps 2.92
+//   1024^2     24 x 24, 5 steps 7.4   32 x 16, 5 steps 8.3   56 x 8, 5 steps 7.7
+// Grids of few rows (columns): the tile spans them, so that only the long axis has a halo and
+// more steps fit (4096 x 4: 32 columns, 17 steps 0.54; 9 steps 0.68).
 TilePlan tile_plan(int nx, int ny)
 {
     TilePlan p{};
-    const long long n16 = (long long)((nx + 15) / 16) * ((ny + 15) / 16);
-    const int thin = std::min(nx, ny);
-    if (thin <= 8 && std::max(nx, ny) > 64) {
-        p.steps = 17;
-        p.tx = nx <= ny ? nx : 32;
-        p.ty = nx <= ny ? 32 : ny;
-    } else if (n16 <= 256) {
-        p.steps = 9;
-        p.tx = p.ty = 16;
-    } else {
-        p.steps = 5;
-        p.tx = 32;
-        p.ty = 16;
+    auto fits = [&](int steps, int tx, int ty) {
+        p.steps = steps;
+        p.tx = tx;
+        p.ty = ty;
+        return (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) <= 256;
+    };
+    if (std::min(nx, ny) <= 8 && std::max(nx, ny) > 64) {
+        if (nx <= ny)
+            fits(17, nx, 32);
+        else
+            fits(17, 32, ny);
+    } else if (!fits(9, 4, 4) && !fits(9, 8, 8) && !fits(9, 16, 16) && !fits(7, 20, 18) && !fits(5, 32, 16)) {
+        fits(5, 24, 24);
     }
     p.tx = std::min(p.tx, nx);
     p.ty = std::min(p.ty, ny);

@@ -12,11 +12,16 @@
 // Node arithmetic, rounding of 16-bit storage between steps and bits are those of the single
 // step. Between the steps bounced populations come from the node's own registers.
 //
-// What bounds it: a launch and the first reads (3 us on a tiny grid, 6 us at 512 x 256), then
-// about 1 us per step on a full chip (the VALU at 2 - 4 waves per SIMD, and a barrier).
-// Measured on MI355X, FP32 with solids, us per step against single steps: 64 x 32 1.4 (2.8),
-// 4096 x 4 0.7 (3.1), 256 x 256 1.6 (3.8), 512 x 256 2.5 (4.0), 512 x 512 3.7 (6.0),
-// 1024 x 512 7.0 (9.4).
+// What bounds it: a launch and the first reads (3 us), then the VALU and one barrier per step:
+// 0.4 us per step with one wavefront per SIMD, 1 us with four; on grids of many tiles the VALU
+// with its recomputed halo (a 24 x 24 tile with 5 steps: 1.55 times the nodes). So the first
+// reads wait for nothing (both places a population may sit in are loaded beside the link
+// mask), a thread's LDS places are laid out once and its last step is one compare, and the
+// loop takes two steps, one per LDS half: 64 x 32 12.0 -> 9.4 us per launch of 9 steps, 4096 x 4
+// 11.6 -> 9.2 (17 steps), 512 x 256 12.3 -> 11.0 (5 steps).
+// Measured on MI355X, FP32 with solids, us per step against single steps: 64 x 32 0.75 (2.8),
+// 4096 x 4 0.54 (3.1), 256 x 256 1.4 (3.8), 512 x 256 2.2 (4.0), 512 x 512 2.9 (6.0),
+// 1024 x 512 4.5 (9.4), 2048 x 1024 13.4.
 #pragma once
 
 #include "lbm_device.h"
@@ -28,7 +33,8 @@ struct TileArgs {
     StepArgs a;
     TilePlan p;
     int steps;
-    FastDiv div_rx, div_ntx;
+    FastDiv div_rx, div_ntx, div_nx, div_ny;
+    int xoff, yoff;  // first node of tile 0's region, plus multiples of nx, ny that make it >= 0
     uint32_t keys[kTileSteps];  // sr_key of the steps but the last
     uint32_t last_key;          // sr_key of the last step
 };
@@ -51,10 +57,11 @@ __global__ __launch_bounds__(kTileThreads) void k_tile(TileArgs ta)
     const int bid = (int)blockIdx.x, tyi = fast_div(bid, ta.div_ntx), txi = bid - tyi * ta.p.ntx;
     const int id = (int)threadIdx.x;
     const int j = fast_div(id, ta.div_rx), i = id - j * rx;
-    const bool in = j < ry;
-    int x = (txi * ta.p.tx - hx * (steps - 1) + i) % nx, y = (tyi * ta.p.ty - hy * (steps - 1) + j) % ny;
-    if (x < 0) x += nx;
-    if (y < 0) y += ny;
+    const int xv = txi * ta.p.tx + ta.xoff + i, yv = tyi * ta.p.ty + ta.yoff + j;
+    const int x = xv - nx * fast_div(xv, ta.div_nx), y = yv - ny * fast_div(yv, ta.div_ny);
+    // steps after the first that the node takes: its inputs of step l + 1 are exact inside the
+    // region shrunk by l
+    const int more = j < ry ? min(hx ? min(i, rx - 1 - i) : steps, hy ? min(j, ry - 1 - j) : steps) : -1;
     Tile t{};
     t.x0 = x;
     t.y = y;
@@ -79,17 +86,30 @@ __global__ __launch_bounds__(kTileThreads) void k_tile(TileArgs ta)
     });
     LT lk[1] = {0};
     float d[1][L::Q], o[1][L::Q], s = 0.f;
-    if (in) {
+    if (more >= 0) {
+        // Step 1. Own slot: the pulled value and the node's own slot qbar are both loaded, so
+        // that neither waits for the link mask (the state is far below 4 GiB here)
+        const PullRows r = pull_rows<1>(g, t);
+        const T *src = static_cast<const T *>(a.src);
+        constexpr bool kOwn = MASK && !kSolidSlotBB<ST>;
+        T c[L::Q], own[L::Q];
         if (MASK) lk[0] = *at32(static_cast<const LT *>(a.links), (unsigned)t.own);
-        gather_tile<LAT, ST, MASK, 1>(g, static_cast<const T *>(a.src), 1.f, t, lk, d);
+        for_q<L::Q>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            c[q] = *at32(src, (unsigned)pull_row<LAT, q>(g, t, r) + pull_x<LAT, q, 1>(r, 0));
+            if constexpr (kOwn && q != 0)
+                own[q] = *at32(src, (unsigned)L::opp[q] * (unsigned)g.stride + (unsigned)t.own);
+        });
         if (SOFT) s = *at32(g.s, (unsigned)t.own);
+        for_q<L::Q>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            d[0][q] = Codec<ST>::dec(c[q], 1.f);
+            if constexpr (kOwn && q != 0) d[0][q] = link_select<q>(lk[0], Codec<ST>::dec(own[q], 1.f), d[0][q]);
+        });
         collide<LAT, SOFT, FORCE>(a.ph, d[0], s, o[0]);
     }
-    for (int l = 1; l < steps; ++l) {
-        // the node's inputs of step l + 1 are exact inside the region shrunk by l
-        const bool live = in && i >= l * hx && i < rx - l * hx && j >= l * hy && j < ry - l * hy;
-        float(&buf)[L::Q - 1][kTileThreads] = sh[l & 1];
-        if (in) {
+    auto step = [&](int l, float(&buf)[L::Q - 1][kTileThreads]) {
+        if (more >= l - 1) {
             if constexpr (ST != LBM_F32) {  // what step l stores
                 const uint32_t h = SR ? sr_node((uint32_t)t.own, ta.keys[l - 1]) : 0u;
 #pragma unroll
@@ -99,23 +119,25 @@ __global__ __launch_bounds__(kTileThreads) void k_tile(TileArgs ta)
             for (int q = 1; q < L::Q; ++q) buf[q - 1][id] = o[0][q];
         }
         __syncthreads();
-        if (live) {
+        if (more >= l) {
             d[0][0] = o[0][0];
             const float *flat = &buf[0][0];
 #pragma unroll
             for (int q = 1; q < L::Q; ++q) d[0][q] = flat[from[q]];
-            if constexpr (MASK) {
-                // (opaque, so that the reads stay one batch instead of a branch per link)
-#pragma unroll
-                for (int q = 1; q < L::Q; ++q) asm volatile("" : "+v"(d[0][q]));
-#pragma unroll
-                for (int q = 1; q < L::Q; ++q) d[0][q] = (lk[0] >> q) & 1u ? o[0][L::opp[q]] : d[0][q];
-            }
+            if constexpr (MASK)
+                for_q<L::Q>([&](auto qc) {
+                    constexpr int q = decltype(qc)::value;
+                    if constexpr (q != 0) d[0][q] = link_select<q>(lk[0], o[0][L::opp[q]], d[0][q]);
+                });
             collide<LAT, SOFT, FORCE>(a.ph, d[0], s, o[0]);
         }
+    };
+    for (int l = 1; l < steps; l += 2) {  // (an even number of steps after the first)
+        step(l, sh[1]);
+        step(l + 1, sh[0]);
     }
     const int ox = i - hx * (steps - 1), oy = j - hy * (steps - 1);
-    if (in && ox >= 0 && ox < ta.p.tx && oy >= 0 && oy < ta.p.ty && txi * ta.p.tx + ox < nx && tyi * ta.p.ty + oy < ny) {
+    if (more >= 0 && ox >= 0 && ox < ta.p.tx && oy >= 0 && oy < ta.p.ty && txi * ta.p.tx + ox < nx && tyi * ta.p.ty + oy < ny) {
         const uint32_t h[1] = {SR ? sr_node((uint32_t)t.own, ta.last_key) : 0u};
         store_tile<LAT, ST, MASK, 1, SR, false, false>(g, static_cast<T *>(a.dst), t, lk, o, h);
     }
@@ -128,7 +150,7 @@ hipError_t tile_launch(const TileArgs &ta, int threads, hipStream_t st)
     return hipGetLastError();
 }
 
-// `steps` time steps (1 .. p.steps) from a.src into a.dst with the step keys `keys`.
+// `steps` time steps (odd, 1 .. p.steps) from a.src into a.dst with the step keys `keys`.
 template <int ST, bool SR>
 hipError_t tile_st(int force, const StepArgs &a, const TilePlan &p, int steps, const uint32_t *keys, hipStream_t st)
 {
@@ -140,9 +162,14 @@ hipError_t tile_st(int force, const StepArgs &a, const TilePlan &p, int steps, c
     const int rx = p.tx + (p.tx < a.g.nx ? 2 * (steps - 1) : 0), ry = p.ty + (p.ty < a.g.ny ? 2 * (steps - 1) : 0);
     ta.div_rx = make_fastdiv(rx);
     ta.div_ntx = make_fastdiv(p.ntx);
+    ta.div_nx = make_fastdiv(a.g.nx);
+    ta.div_ny = make_fastdiv(a.g.ny);
+    auto first = [&](int halo, int n) { return (halo + n - 1) / n * n - halo; };
+    ta.xoff = first((rx - p.tx) / 2, a.g.nx);
+    ta.yoff = first((ry - p.ty) / 2, a.g.ny);
     for (int k = 0; k < steps; ++k) ta.keys[k] = ta.last_key = keys[k];
     const int threads = (rx * ry + 63) / 64 * 64;
-    if (steps < 1 || steps > kTileSteps || threads > kTileThreads) return hipErrorInvalidValue;
+    if (steps % 2 == 0 || steps < 1 || steps > kTileSteps || threads > kTileThreads) return hipErrorInvalidValue;
 #define LBM_TILE(M, S, F) \
     return M && slip ? tile_launch<ST, M, S, F, M, SR>(ta, threads, st) : tile_launch<ST, M, S, F, false, SR>(ta, threads, st)
 #define LBM_TILE_F(M, S)                   \

@@ -56,6 +56,21 @@ def test_same_bits_as_single_steps(nx, ny, storage, rounding, kind):
         assert torch.equal(one.export_f64(), many.export_f64()), steps
 
 
+# strips with solids in every storage format (N >= 2.5 M in FP32, >= 8 M in 16 bits), tiles of each plan:
+# 4 x 4, 8 x 8 and 20 x 18 nodes a block, exactly 256 of them, and one more along an axis
+@pytest.mark.parametrize("kind", ["open", "walls", "soft", "slip"])
+@pytest.mark.parametrize("storage,rounding", [("f32", "nearest"), ("f16", "nearest"), ("bf16", "stochastic")])
+@pytest.mark.parametrize("nx,ny", [(225, 36001), (65537, 123), (350000, 23), (64, 64), (65, 64), (17, 45), (128, 128),
+                                   (100, 129), (320, 288), (319, 271), (530, 501)])
+def test_same_bits_on_larger_strips_and_each_plan(nx, ny, storage, rounding, kind):
+    steps = 16 if nx * ny < 655360 else 8  # 9 + 7 or 7 + 7 + 1 + 1, 5 + 3
+    one, many = (_sim(nx, ny, storage, rounding, kind) for _ in range(2))
+    for _ in range(steps):
+        one.step(1)
+    many.step(steps)
+    assert torch.equal(one.export_f64(), many.export_f64(many.bufs[0]))
+
+
 @pytest.mark.parametrize("nx,ny", [(300, 290), (1120, 600)])
 def test_captured_steps_replay(nx, ny):
     """A graph of an even number of steps advances the state on every replay."""
