@@ -299,12 +299,11 @@ int force_level(const lbm_t h)
 bool has_solids(const lbm_t h) { return h->mask != nullptr || h->p.slip != 0; }
 const void *links_of(const lbm_t h) { return has_solids(h) ? h->links : nullptr; }
 // How several steps go into one launch, on two state buffers. D2V9: tiles on small grids, whose
-// single step is a launch and little else; from there on strips in registers, whose one pass
-// over memory serves five steps. The line is where both measured the same (us per step, tiles /
-// strips): FP32 1024 x 800 5.8 / 5.8, 2048 x 1024 11.8 / 11.0; with solids 2048 x 1024
-// 13.4 / 14.7, 2048^2 27.2 / 26.9; FP16 2048^2 20.8 / 21.5, 3000 x 2000 28.9 / 27.6; with solids
-// 2048^2 24.5 / 27.5 (stochastic 25.9 / 28.7), 3000 x 2000 35.2 / 36.4, 4096^2 98.9 / 85.3 (the
-// strips pay for a mask with registers, and narrow 16-bit rows with partly filled lines).
+// single step is a launch and little else, up to the size where strips in registers, which
+// recompute less, measured the same in every format, with solids and without (us per step,
+// tiles / strips): FP32 2048^2 19.2 / 22.1, 4096 x 2048 38.9 / 38.9, 4096^2 76.0 / 69.4; with
+// solids 23.2 / 27.4, 46.7 / 47.2, 91.7 / 82.2; FP16 18.1 / 21.8, 36.0 / 36.0, 71.0 / 63.2; FP16
+// with solids, stochastic 28.3 / 31.3, 56.4 / 56.8, 111 / 103.
 // D3V19: blocks marching along z, two steps per launch, where the grid
 // fills them (us per step, two / one per launch: FP32 128 x 64 x 64 14.1 / 15.9, 64^3
 // 17.6 / 11.6) and memory, not the VALU, bounds the single step: 16-bit states that stay in
@@ -322,9 +321,7 @@ MultiStep multi_step(const lbm_t h)
         return h->N >= (h->p.storage == LBM_F32 ? 500000 : (plain ? 2000000 : 8000000)) ? kMultiMarch3 : kMultiNone;
     }
     if (h->p.lattice != LBM_D2V9) return kMultiNone;
-    const int64_t tiles = h->p.storage == LBM_F32 ? (has_solids(h) ? 2500000 : 800000)
-                                                  : (has_solids(h) ? 8000000 : 5000000);
-    return h->N < tiles ? kMultiTile : kMultiMarch;
+    return h->N < 8000000 ? kMultiTile : kMultiMarch;
 }
 bool adjoint_supported(const lbm_t h) { return !h->thermal; }
 

@@ -21,8 +21,7 @@
 // lanes, of which 56 are written; FP32 4096^2 issues VALU 70 % of the time), no longer memory:
 // on that grid a launch of two steps took 320 us, of three 330 us, of five 350 us, against
 // 190 us for one single step. Measured on MI355X, us per step against single steps: periodic
-// 4096^2 FP32 70 (190), FP16 65 (101); disks 2048^2 FP32 28.5 (55), FP16 with stochastic
-// rounding 33 (37); 1531 x 1117 disks FP32 12.8 (33). Two nodes per lane (fewer lanes lost
+// 4096^2 FP32 70 (190), FP16 63 (101); with disks FP32 82, FP16 86. Two nodes per lane (fewer lanes lost
 // at the strips' edges) measured the same in FP32 and 20 % slower in 16 bits (twice the
 // registers, half the waves); streamed stores 5 % slower (neighbouring waves complete the
 // lines at the strips' edges in the cache).

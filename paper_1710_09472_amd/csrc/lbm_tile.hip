@@ -6,16 +6,17 @@
 
 namespace lbm {
 
-// Tiles by measurement: the most steps whose tiles still fit the 256 CUs about once (a second
-// block per CU takes turns with the first), on the smallest tiles that do (fewer wavefronts
-// per SIMD). us per step, FP32 with solids:
-//   64 x 32    4 x 4, 9 steps 0.75    8 x 8, 9 steps 0.86    16 x 16, 9 steps 1.04
-//   128 x 128  8 x 8, 9 steps 0.94    16 x 16, 9 steps 1.06  8 x 8, 5 steps 1.03
-//   256 x 256  16 x 16, 9 steps 1.36  16 x 16, 5 steps 1.67  16 x 8, 9 steps 1.48
-//   300 x 290  20 x 18, 7 steps 1.87  16 x 16, 9 steps 1.96  32 x 16, 5 steps 1.99
-//   512 x 256  32 x 16, 5 steps 2.19  20 x 12, 7 steps 2.29  32 x 16, 3 steps 2.91
-//   512 x 512  24 x 24, 5 steps 2.91  32 x 16, 5 steps 2.92
-//   1024^2     24 x 24, 5 steps 7.4   32 x 16, 5 steps 8.3   56 x 8, 5 steps 7.7
+// Tiles by measurement: the most steps whose tiles fit the 256 CUs once (a second block per CU
+// takes turns with the first), on the smallest tiles that do (fewer wavefronts per SIMD). us per
+// step, FP32 with solids:
+//   64 x 32    4 x 4, 9 steps 0.76    8 x 8, 9 steps 0.86    16 x 16, 9 steps 1.04
+//   128 x 128  8 x 8, 9 steps 0.92    16 x 16, 9 steps 1.07  8 x 8, 11 steps 0.94
+//   256 x 256  16 x 16, 9 steps 1.18  16 x 16, 7 steps 1.25  32 x 16, 5 steps 1.44
+//   300 x 290  20 x 18, 7 steps 1.46  16 x 16, 9 steps 1.69  24 x 24, 5 steps 1.58
+// and 24 x 24 with 5 steps on every larger grid:
+//   512 x 256  24 x 24, 5 steps 1.59  32 x 16, 5 steps 1.63  20 x 18, 7 steps 1.83
+//   512 x 512  24 x 24, 5 steps 2.21  32 x 16, 5 steps 2.38  28 x 28, 3 steps 2.91
+//   2048^2     24 x 24, 5 steps 23.2  32 x 16, 5 steps 29.3  56 x 8, 5 steps 25.4
 // Grids of few rows (columns): the tile spans them, so that only the long axis has a halo and
 // more steps fit (4096 x 4: 32 columns, 17 steps 0.54; 9 steps 0.68).
 TilePlan tile_plan(int nx, int ny)
@@ -32,7 +33,7 @@ TilePlan tile_plan(int nx, int ny)
             fits(17, nx, 32);
         else
             fits(17, 32, ny);
-    } else if (!fits(9, 4, 4) && !fits(9, 8, 8) && !fits(9, 16, 16) && !fits(7, 20, 18) && !fits(5, 32, 16)) {
+    } else if (!fits(9, 4, 4) && !fits(9, 8, 8) && !fits(9, 16, 16) && !fits(7, 20, 18)) {
         fits(5, 24, 24);
     }
     p.tx = std::min(p.tx, nx);

@@ -18,10 +18,10 @@
 // reads wait for nothing (both places a population may sit in are loaded beside the link
 // mask), a thread's LDS places are laid out once and its last step is one compare, and the
 // loop takes two steps, one per LDS half: 64 x 32 12.0 -> 9.4 us per launch of 9 steps, 4096 x 4
-// 11.6 -> 9.2 (17 steps), 512 x 256 12.3 -> 11.0 (5 steps).
-// Measured on MI355X, FP32 with solids, us per step against single steps: 64 x 32 0.75 (2.8),
-// 4096 x 4 0.54 (3.1), 256 x 256 1.4 (3.8), 512 x 256 2.2 (4.0), 512 x 512 2.9 (6.0),
-// 1024 x 512 4.5 (9.4), 2048 x 1024 13.4.
+// 11.6 -> 9.2 (17 steps), 512 x 256 12.3 -> 11.0 (5 steps; 8.1 with slabs per XCD).
+// Measured on MI355X, FP32 with solids, us per step against single steps: 64 x 32 0.76 (2.8),
+// 4096 x 4 0.54 (3.1), 256 x 256 1.2 (3.8), 512 x 256 1.6 (4.0), 512 x 512 2.2 (6.0),
+// 1024 x 512 3.8 (9.4), 2048^2 23.2.
 #pragma once
 
 #include "lbm_device.h"
@@ -54,7 +54,10 @@ __global__ __launch_bounds__(kTileThreads) void k_tile(TileArgs ta)
     // halo along each axis (0 where the tile spans the axis) and the block's region rx x ry
     const int hx = ta.p.tx < nx ? 1 : 0, hy = ta.p.ty < ny ? 1 : 0;
     const int rx = ta.p.tx + 2 * hx * (steps - 1), ry = ta.p.ty + 2 * hy * (steps - 1);
-    const int bid = (int)blockIdx.x, tyi = fast_div(bid, ta.div_ntx), txi = bid - tyi * ta.p.ntx;
+    // blocks in contiguous slabs per XCD: what a tile reads beyond its edge, and the lines it
+    // shares with its neighbours, are then in the L2 that wrote them (512 x 256 FP32 11.0 ->
+    // 8.1 us per launch, 256 x 256 12.4 -> 10.6, 2048^2 130 -> 116; 64 x 32 6.8 -> 6.9)
+    const int bid = xcd_remap((int)blockIdx.x, (int)gridDim.x), tyi = fast_div(bid, ta.div_ntx), txi = bid - tyi * ta.p.ntx;
     const int id = (int)threadIdx.x;
     const int j = fast_div(id, ta.div_rx), i = id - j * rx;
     const int xv = txi * ta.p.tx + ta.xoff + i, yv = tyi * ta.p.ty + ta.yoff + j;

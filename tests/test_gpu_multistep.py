@@ -10,7 +10,7 @@ from paper_1710_09472_amd import lbm
 
 pytestmark = pytest.mark.gpu
 
-# nx, ny: tiles (one block, ragged tiles, thin grids), strips (N >= 655360 in FP32, >= 1310720 in 16 bits)
+# nx, ny: tiles (one block, ragged tiles, thin grids), larger grids of odd shapes
 TILES = [(1, 1), (5, 3), (16, 16), (33, 18), (70, 9), (300, 5), (4, 131), (301, 290), (1000, 640)]
 STRIPS = [(56, 24000), (223, 5900), (225, 5861), (1120, 1171), (65537, 21), (350000, 4)]
 
@@ -56,7 +56,7 @@ def test_same_bits_as_single_steps(nx, ny, storage, rounding, kind):
         assert torch.equal(one.export_f64(), many.export_f64()), steps
 
 
-# strips with solids in every storage format (N >= 2.5 M in FP32, >= 8 M in 16 bits), tiles of each plan:
+# strips in every storage format (N >= 8 M), tiles of each plan:
 # 4 x 4, 8 x 8 and 20 x 18 nodes a block, exactly 256 of them, and one more along an axis
 @pytest.mark.parametrize("kind", ["open", "walls", "soft", "slip"])
 @pytest.mark.parametrize("storage,rounding", [("f32", "nearest"), ("f16", "nearest"), ("bf16", "stochastic")])
