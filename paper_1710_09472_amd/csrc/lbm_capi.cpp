@@ -304,11 +304,13 @@ const void *links_of(const lbm_t h) { return has_solids(h) ? h->links : nullptr;
 // tiles / strips): FP32 2048^2 19.2 / 22.1, 4096 x 2048 38.9 / 38.9, 4096^2 76.0 / 69.4; with
 // solids 23.2 / 27.4, 46.7 / 47.2, 91.7 / 82.2; FP16 18.1 / 21.8, 36.0 / 36.0, 71.0 / 63.2; FP16
 // with solids, stochastic 28.3 / 31.3, 56.4 / 56.8, 111 / 103.
-// D3V19: blocks marching along z, two steps per launch, where the grid
-// fills them (us per step, two / one per launch: FP32 128 x 64 x 64 14.1 / 15.9, 64^3
-// 17.6 / 11.6) and memory, not the VALU, bounds the single step: 16-bit states that stay in
-// the 256 MB Infinity Cache do not gain with solids or stochastic rounding (FP16 duct
-// 256 x 128 x 128 61.4 / 58.5, 256^3 duct 222 / 249; FP16 128^3 periodic 28.0 / 32.4). The
+// D3V19: blocks marching along z, two steps per launch, where the grid fills them (FP32
+// 128 x 64 x 64 14.1 / 15.9 us per step with two / one per launch, 64^3 17.6 / 11.6) and memory
+// bounds the single step. That holds for FP32 always (128^3 42 - 50 / 59 - 66, 256 x 256 x 128
+// 148 - 179 / 232 - 265), for 16-bit states with solids beyond the 256 MB Infinity Cache
+// (256 x 256 x 128 158 - 184 / 269 - 280; 128^3 no gain), and for 16-bit ones without solids where
+// neither a source term nor stochastic rounding adds to the VALU's work (FP16 128^3 28 - 30 /
+// 32 - 34; with a source 31 - 36 / 33 - 35, stochastic 256 x 256 x 128 124 - 142 / 114 - 120). The
 // reads of bounced links take 32-bit offsets (FP32 with solids: states below 4 GiB).
 enum MultiStep { kMultiNone, kMultiTile, kMultiMarch, kMultiMarch3 };
 MultiStep multi_step(const lbm_t h)
@@ -317,10 +319,21 @@ MultiStep multi_step(const lbm_t h)
     const size_t bytes = (size_t)h->Q * (size_t)h->stride * h->elem;
     if (h->p.storage == LBM_F32 && has_solids(h) && bytes >= (1ull << 32)) return kMultiNone;
     if (h->p.lattice == LBM_D3V19) {
-        const bool plain = !has_solids(h) && h->p.rounding == LBM_ROUND_NEAREST;
-        return h->N >= (h->p.storage == LBM_F32 ? 500000 : (plain ? 2000000 : 8000000)) ? kMultiMarch3 : kMultiNone;
+        if (h->p.storage == LBM_F32) return h->N >= 500000 ? kMultiMarch3 : kMultiNone;
+        if (has_solids(h)) return h->N >= 8000000 ? kMultiMarch3 : kMultiNone;
+        const int force = force_level(h);
+        const bool plain = h->p.rounding == LBM_ROUND_NEAREST && (force == 0 || force == 3);
+        return plain && h->N >= 2000000 ? kMultiMarch3 : kMultiNone;
     }
     if (h->p.lattice != LBM_D2V9) return kMultiNone;
+    // The one exception: states in the Infinity Cache without solids, where stochastic rounding, a
+    // source term and a porosity field or magnetic term together bound the single step by the
+    // VALU too, and tiles repeat that work in their halos (FP16 2048^2 tiles / single steps with E
+    // and B 31.9 / 30.5, with E and porosity 33.3 / 31.7, both 35.9 / 32.2).
+    const int force = force_level(h);
+    if (h->p.rounding != LBM_ROUND_NEAREST && !has_solids(h) && (force == 2 || (force == 1 && h->g.s)) &&
+        h->N >= 2000000 && h->N < 6000000)
+        return kMultiNone;
     return h->N < 8000000 ? kMultiTile : kMultiMarch;
 }
 bool adjoint_supported(const lbm_t h) { return !h->thermal; }

@@ -680,16 +680,17 @@ __device__ __forceinline__ Macro<LAT> macro(const Physics &p, const float *d)
 // sigma_q = (e_q.c1v) + c2q (e_q.U) + C2_k c_s (U.E) + C2_k e_q.(U x B). The rest population
 // follows from mass closure (relaxation and source conserve mass), o_0 = sum_q D_q -
 // sum_{q>0} o_q, which also keeps FP32 mass conservation exact up to one rounding per node.
-// The force constants are odd in e_q: one scalar register serves a pair of opposite
-// populations (half of the 2 x 18 of D3V19, which otherwise spill to vector lanes).
-template <int LAT, int q>
+// The force constants are odd in e_q: with PAIRED one scalar register serves a pair of opposite
+// populations (half of the 2 x 18 of D3V19, which otherwise spill to vector lanes in k_march3;
+// the single D3V19 step has the registers and measured 1 % faster without).
+template <int LAT, int q, bool PAIRED>
 __device__ __forceinline__ float odd_const(const float *c)
 {
     constexpr int p = Lat<LAT>::opp[q];
-    return q < p ? c[q] : -c[p];
+    return !PAIRED || q < p ? c[q] : -c[p];
 }
 
-template <int LAT, int FORCE>
+template <int LAT, int FORCE, bool PAIRED>
 __device__ __forceinline__ void relax_node(const Physics &p, const float *D, float *o)
 {
 #pragma clang fp contract(off)
@@ -743,9 +744,9 @@ __device__ __forceinline__ void relax_node(const Physics &p, const float *D, flo
             if constexpr (FORCE == 0 || FORCE == 3)
                 inner = __builtin_fmaf(p.omBc * eu, eu, P[k]);
             else if constexpr (FORCE == 1)
-                inner = __builtin_fmaf(__builtin_fmaf(p.omBc, eu, odd_const<LAT, q>(p.c2q)), eu, P[k] + odd_const<LAT, q>(p.c1q));
+                inner = __builtin_fmaf(__builtin_fmaf(p.omBc, eu, odd_const<LAT, q, PAIRED>(p.c2q)), eu, P[k] + odd_const<LAT, q, PAIRED>(p.c1q));
             else
-                inner = __builtin_fmaf(__builtin_fmaf(p.omBc, eu, odd_const<LAT, q>(p.c2q)), eu, P[k] + edot<LAT, q>(H[k]));
+                inner = __builtin_fmaf(__builtin_fmaf(p.omBc, eu, odd_const<LAT, q, PAIRED>(p.c2q)), eu, P[k] + edot<LAT, q>(H[k]));
             const float v = __builtin_fmaf(wr[k], inner,
                                            __builtin_fmaf(p.ol[k], ej, __builtin_fmaf(p.c0, D[q], owd[k])));
             o[q] = v;
@@ -755,12 +756,12 @@ __device__ __forceinline__ void relax_node(const Physics &p, const float *D, flo
     o[0] = drho - sum;
 }
 
-template <int LAT, bool SOFT, int FORCE>
+template <int LAT, bool SOFT, int FORCE, bool PAIRED = LAT == LBM_D2V9>
 __device__ __forceinline__ void collide(const Physics &p, const float *D, float s, float *o)
 {
 #pragma clang fp contract(off)
     using L = Lat<LAT>;
-    relax_node<LAT, FORCE>(p, D, o);
+    relax_node<LAT, FORCE, PAIRED>(p, D, o);
     if (SOFT) {
         float t[L::Q];
 #pragma unroll

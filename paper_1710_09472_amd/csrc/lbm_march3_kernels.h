@@ -153,7 +153,7 @@ __global__ __launch_bounds__(kM3Threads, 4) void k_march3(March3Args ma)
             float d[L::Q];
 #pragma unroll
             for (int q = 0; q < L::Q; ++q) d[q] = Codec<ST>::dec(c[q], 1.f);
-            collide<LAT, SOFT, FORCE>(a.ph, d, s, o);
+            collide<LAT, SOFT, FORCE, true>(a.ph, d, s, o);
             if constexpr (ST != LBM_F32) {  // what step 1 stores
                 const uint32_t h = SR ? sr_node((uint32_t)(xi + nx * (yv + ny * z)), ma.key[0]) : 0u;
 #pragma unroll
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(kM3Threads, 4) void k_march3(March3Args ma)
             s_prev = s;
             if (it >= 2) {
                 float o2[1][L::Q];
-                collide<LAT, SOFT, FORCE>(a.ph, e, s2, o2[0]);
+                collide<LAT, SOFT, FORCE, true>(a.ph, e, s2, o2[0]);
                 Tile t{};
                 t.x0 = xi;
                 t.y = ys;
