@@ -7,9 +7,12 @@ A timed step is one fused collide-and-stream update of every node (pull streamin
 moments, equilibrium, Lorentz source, BGK relaxation, store) in FP32 arithmetic with
 FP32 deviation storage, inputs resident in HBM.
 
-Prints one JSON line: MLUPS (value), ms per step, the roofline of the step kernel
-(algorithmic bytes per launch / measured average launch time, against 8 TB/s HBM3E),
-the FP16- and BF16-storage steps, the adjoint step relative to the forward step, the
+The library takes several steps per launch where that pays (five on this grid: every
+population then passes through memory once per five steps, and the vector ALU is the bound).
+
+Prints one JSON line: MLUPS (value), ms per step, the roofline of the timed kernel
+(algorithmic bytes per launch / measured average launch time, against 8 TB/s HBM3E) and of
+the single-step kernel beside it, the FP16- and BF16-storage steps, the adjoint step relative to the forward step, the
 in-place step (one state buffer, FP32 and FP16) with its two phases, and the FP64 CPU
 oracle timed on this host on a bounded sample of the same workload.
 
@@ -119,7 +122,7 @@ def algorithmic_bytes(wl, Q: int, elem: int) -> int:
 
 
 def timed_steps(sim, steps: int, warmup: int):
-    """Warm up, then time `steps` launches with HIP events on the library's stream
+    """Warm up, then time `steps` steps with HIP events on the library's stream
     (torch's current stream) and with the host clock; both bracketed by synchronize."""
     import torch
 
@@ -133,6 +136,45 @@ def timed_steps(sim, steps: int, warmup: int):
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     return wall, ev0.elapsed_time(ev1) * 1e-3
+
+
+def launch_plan(wl, storage: str, rounding: str = "nearest", inplace: bool = False):
+    """(kernel, steps per launch) of a long run of the workload: the library's rule (lbm_capi.cpp
+    multi_step, lbm_tile.hip tile_plan)."""
+    if wl.lattice == "D1V7":
+        return ("k_thermal_aa_pull+k_thermal_aa_local", 1) if inplace else ("k_thermal_multi", 5)
+    if inplace:
+        return "k_step_aa_pull+k_step_aa_local", 1
+    solids = wl.mask is not None or bool(wl.slip)
+    if wl.lattice == "D3V19":
+        plain = rounding == "nearest" and (wl.forcing == "shift" or not any((*wl.E, *wl.B)))
+        least = 500000 if storage == "f32" else 8000000 if solids else 2000000 if plain else wl.N + 1
+        return ("k_march3", 2) if wl.N >= least else ("k_step", 1)
+    source = wl.forcing == "source" and any((*wl.E, *wl.B))
+    if rounding != "nearest" and not solids and source and (wl.s is not None or any(wl.B)) and 2e6 <= wl.N < 6e6:
+        return "k_step", 1
+    if wl.N >= 8000000:
+        return "k_march", 5
+    if min(wl.nx, wl.ny) <= 8 and max(wl.nx, wl.ny) > 64:
+        return "k_tile", 17
+    for steps, tx, ty in ((9, 4, 4), (9, 8, 8), (9, 16, 16), (7, 20, 18)):
+        if -(-wl.nx // tx) * -(-wl.ny // ty) <= 256:
+            return "k_tile", steps
+    return "k_tile", 5
+
+
+def single_steps(sim, steps: int):
+    """Average duration of a one-step launch: `steps` calls of one step each."""
+    import torch
+
+    torch.cuda.synchronize()
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    e0.record(sim.stream)
+    for _ in range(steps):
+        sim.step(1)
+    e1.record(sim.stream)
+    torch.cuda.synchronize()
+    return e0.elapsed_time(e1) * 1e-3 / steps
 
 
 def inplace_phases(sim, steps: int):
@@ -182,14 +224,15 @@ def thermal_extra(steps: int, warmup: int):
     w, e = timed_steps(sim, steps, warmup)
     alg = algorithmic_bytes(wl, sim.Q, 4)
     sim.close()
-    gbs = alg / (e / steps) / 1e9
+    per = launch_plan(wl, "f32")[1]
+    gbs = alg / (e / steps * per) / 1e9
     one = Simulation(wl.lattice, wl.nx, wl.ny, wl.nz, tau=wl.tau, theta=wl.theta, mu=wl.mu, inplace=True)
     one.init(wl.rho, wl.u, wl.thetabar)
     w1, e1 = timed_steps(one, steps, warmup + (warmup % 2))
     one.close()
     out = {"workload": "thermal_1d: D1V7 2^24 nodes, K = 4, FP32", "MLUPS": round(wl.N * steps / w / 1e6, 1),
            "ms_per_step": round(w / steps * 1e3, 5), "achieved_GBs": round(gbs, 1),
-           "hbm_frac": round(gbs / 8000.0, 4),
+           "hbm_frac": round(gbs / 8000.0, 4), "steps_per_launch": per,
            "inplace": {"MLUPS": round(wl.N * steps / w1 / 1e6, 1), "ms_per_step": round(w1 / steps * 1e3, 5),
                        "achieved_GBs": round(alg / (e1 / steps) / 1e9, 1), "state_buffers": 1}}
     # FP16 storage (x 2^17), two state buffers and in place
@@ -200,10 +243,12 @@ def thermal_extra(steps: int, warmup: int):
         s16.init(wl.rho, wl.u, wl.thetabar)
         w16, e16 = timed_steps(s16, steps, warmup + (warmup % 2))
         s16.close()
-        g16 = alg16 / (e16 / steps) / 1e9
+        per = launch_plan(wl, "f16", inplace=inplace)[1]
+        g16 = alg16 / (e16 / steps * per) / 1e9
         out["f16_inplace" if inplace else "f16"] = {"MLUPS": round(wl.N * steps / w16 / 1e6, 1),
                                                    "ms_per_step": round(w16 / steps * 1e3, 5),
                                                    "achieved_GBs": round(g16, 1), "hbm_frac": round(g16 / 8000.0, 4),
+                                                   "steps_per_launch": per,
                                                    "dev_scale_log2": F16_SCALE["thermal_1d"]}
     return out
 
@@ -535,10 +580,12 @@ def main():
     else:
         sim.init(wl.rho, wl.u)
     wall, ev = timed_steps(sim, args.steps, args.warmup)
-    t_launch = ev / args.steps
+    name, per = launch_plan(wl, st, args.rounding, args.inplace)
+    t_launch = ev / args.steps * per
     mlups = N * args.steps / wall / 1e6
     alg = algorithmic_bytes(wl, sim.Q, elem)
     achieved = alg / t_launch / 1e9
+    single = None if args.inplace else single_steps(sim, 100)
     traffic = None if (args.inplace or args.rounding != "nearest") else traffic_from_profile(
         f"{'k_thermal_step' if thermal else 'k_step'}_{wl.lattice}_{st}_{args.workload}")
     tot = sim.current()
@@ -557,7 +604,8 @@ def main():
             extras[s16s if rnd == "nearest" else s16s + "_stochastic_rounding"] = {
                 "MLUPS": round(N * args.steps / w16 / 1e6, 1),
                 "ms_per_step": round(w16 / args.steps * 1e3, 5),
-                "achieved_GBs": round(bytes_per_node(s16.Q, 2) * N / t16 / 1e9, 1),
+                "achieved_GBs": round(bytes_per_node(s16.Q, 2) * N / (t16 * per) / 1e9, 1),
+                "steps_per_launch": per,
                 "dev_scale_log2": k}
             s16.close()
         extras["adjoint"] = {}
@@ -575,9 +623,7 @@ def main():
                              "f16": inplace_extra(wl, "f16", F16_SCALE["throughput_2d"], args.steps, args.warmup)}
         extras["thermal"] = thermal_extra(args.steps, args.warmup)
 
-    kernel = ("k_thermal_aa_pull+k_thermal_aa_local" if thermal and args.inplace else
-              "k_thermal_step" if thermal else
-              "k_step_aa_pull+k_step_aa_local" if args.inplace else "k_step") + \
+    instance = \
         f"<{wl.lattice},{st.upper()}" + (",mask" if wl.mask is not None else "") + \
         (",slip" if wl.slip else "") + (",soft" if wl.s is not None else "") + \
         (",shift" if wl.forcing == "shift" else "") + (",stochastic" if args.rounding == "stochastic" else "") + ">"
@@ -598,11 +644,16 @@ def main():
         "dtype": "f32",
         "data": "synthetic",
         "config": {"workload": desc, "lattice": wl.lattice, "nx": wl.nx, "ny": wl.ny, "nz": wl.nz, "storage": st},
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                     "kernel": kernel, "bytes_per_launch": alg,
+        "roofline": {"bound": "hbm" if per == 1 else "latency" if name == "k_march3" else "valu", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                     "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic if per == 1 else None, "steps_per_launch": per,
+                     "kernel": name + instance, "bytes_per_launch": alg,
                      "avg_launch_ms": round(t_launch * 1e3, 5)},
     }
+    if single is not None:
+        out["roofline"]["single_step"] = {
+            "bound": "hbm", "kernel": ("k_thermal_step" if thermal else "k_step") + instance,
+            "avg_launch_ms": round(single * 1e3, 5), "achieved": round(alg / single / 1e9, 1),
+            "frac": round(alg / single / 1e9 / HBM_PEAK_GBS, 4), "traffic": traffic}
     solid = solid_nodes(wl)
     if solid is not None:
         out["fluid_MLUPS"] = round(int((solid == 0).sum()) * args.steps / wall / 1e6, 1)
