@@ -210,7 +210,8 @@ int lbm_init_thermal(lbm_t h, const double *rho, const double *u, const double *
 /* Advance nsteps >= 0 time steps (collide, force, partial bounce-back, stream,
  * halfway bounce-back and free-slip walls: the discrete BGK update of Sec. 9.1 with
  * the forcing of Sec. 7). With one state buffer (state_b = NULL) the steps alternate
- * between the two in-place kernels. Async. */
+ * between the two in-place kernels; with two, several steps go into one launch where that
+ * is faster, with the bits and the state buffer of as many single steps. Async. */
 int lbm_step(lbm_t h, int nsteps);
 
 /* One step of the discrete BGK update of Sec. 9.1 (as lbm_step) from the state in `src`
