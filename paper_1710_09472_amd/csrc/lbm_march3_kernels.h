@@ -291,12 +291,18 @@ hipError_t march3_st(int force, const StepArgs &a, const uint32_t *keys, hipStre
     ma.key[1] = keys[1];
     const dim3 grid(ma.ntx * ma.nty * ((a.g.nz + ma.planes - 1) / ma.planes)), block(kM3Threads);
 #define LBM_M3_K(M, S, F, SL) hipLaunchKernelGGL((k_march3<ST, M, S, F, SL, SR>), grid, block, 0, st, ma)
-#define LBM_M3(M, S, F)               \
-    do {                              \
-        if (M && slip)                \
-            LBM_M3_K(M, S, F, M);     \
-        else                          \
-            LBM_M3_K(M, S, F, false); \
+    // 16-bit states without solids come here only where this kernel beats single steps: rounded
+    // to nearest, without a source term
+#define LBM_M3(M, S, F)                                                    \
+    do {                                                                   \
+        if constexpr (ST == LBM_F32 || M || (!SR && (F == 0 || F == 3))) { \
+            if (M && slip)                                                 \
+                LBM_M3_K(M, S, F, M);                                      \
+            else                                                           \
+                LBM_M3_K(M, S, F, false);                                  \
+        } else {                                                           \
+            return hipErrorInvalidValue;                                   \
+        }                                                                  \
     } while (0)
 #define LBM_M3_F(M, S)   \
     if (force == 0)      \

@@ -133,6 +133,27 @@ def _sim3(nx, ny, nz, storage, rounding, kind):
     return sim
 
 
+# grids on which two steps share a launch (FP32: N >= 500000; 16 bits: N >= 2 M without solids and source
+# term, N >= 8 M with solids): widths around a block's 64 columns, heights around its 13 rows, thin axes
+LARGE3 = [(65, 14, 551), (63, 100, 80), (130, 27, 143), (3, 410, 409), (1, 1000, 501), (700, 751, 1), (1024, 2, 250),
+          (250, 13, 155), (64, 26, 301)]
+
+
+@pytest.mark.parametrize("nx,ny,nz,storage,rounding,kind",
+                         [(*d, "f32", "nearest", k) for d in LARGE3 for k in ("open", "walls", "soft", "slip")]
+                         + [(*d, st, "nearest", "open") for d in [(65, 250, 124), (130, 1027, 15)] for st in ("f16", "bf16")]
+                         + [(*d, *st, k) for d in [(129, 250, 250), (64, 14, 8930)] for k in ("walls", "soft", "slip")
+                            for st in (("f16", "stochastic"), ("bf16", "nearest"))])
+def test_3d_two_steps_per_launch_same_bits(nx, ny, nz, storage, rounding, kind):
+    one, many = (_sim3(nx, ny, nz, storage, rounding, kind) for _ in range(2))
+    for _ in range(9):
+        one.step(1)
+    many.step(9)  # 4 launches of two, one of one
+    fa = one.export_f64()
+    assert torch.equal(fa, many.export_f64())
+    assert torch.equal(fa, many.export_f64(many.bufs[1]))
+
+
 @pytest.mark.parametrize("kind", ["open", "walls", "soft", "slip"])
 @pytest.mark.parametrize("storage,rounding", [("f32", "nearest"), ("f16", "stochastic"), ("bf16", "nearest")])
 @pytest.mark.parametrize("nx,ny,nz", [(1, 1, 1), (3, 2, 5), (64, 13, 9), (65, 14, 7), (63, 12, 3), (128, 26, 40),
