@@ -138,29 +138,14 @@ def timed_steps(sim, steps: int, warmup: int):
     return wall, ev0.elapsed_time(ev1) * 1e-3
 
 
-def launch_plan(wl, storage: str, rounding: str = "nearest", inplace: bool = False):
-    """(kernel, steps per launch) of a long run of the workload: the library's rule (lbm_capi.cpp
-    multi_step, lbm_tile.hip tile_plan)."""
-    if wl.lattice == "D1V7":
-        return ("k_thermal_aa_pull+k_thermal_aa_local", 1) if inplace else ("k_thermal_multi", 5)
-    if inplace:
-        return "k_step_aa_pull+k_step_aa_local", 1
-    solids = wl.mask is not None or bool(wl.slip)
-    if wl.lattice == "D3V19":
-        plain = rounding == "nearest" and (wl.forcing == "shift" or not any((*wl.E, *wl.B)))
-        least = 500000 if storage == "f32" else 8000000 if solids else 2000000 if plain else wl.N + 1
-        return ("k_march3", 2) if wl.N >= least else ("k_step", 1)
-    source = wl.forcing == "source" and any((*wl.E, *wl.B))
-    if rounding != "nearest" and not solids and source and (wl.s is not None or any(wl.B)) and 2e6 <= wl.N < 6e6:
-        return "k_step", 1
-    if wl.N >= 8000000:
-        return "k_march", 5
-    if min(wl.nx, wl.ny) <= 8 and max(wl.nx, wl.ny) > 64:
-        return "k_tile", 17
-    for steps, tx, ty in ((9, 4, 4), (9, 8, 8), (9, 16, 16), (7, 20, 18)):
-        if -(-wl.nx // tx) * -(-wl.ny // ty) <= 256:
-            return "k_tile", steps
-    return "k_tile", 5
+def launch_plan(wl, storage: str, steps: int, rounding: str = "nearest", inplace: bool = False):
+    """(kernel, steps of the largest launch, launches) of a call of `steps` steps of the workload, as
+    the library plans it."""
+    from paper_1710_09472_amd import lbm
+
+    p = lbm.make_params(wl.lattice, wl.nx, wl.ny, wl.nz, tau=wl.tau, E=wl.E, B=wl.B, storage=storage, theta=wl.theta,
+                        mu=wl.mu, forcing=wl.forcing, slip=wl.slip, rounding=rounding)
+    return lbm.launch_plan(p, steps, solids=wl.mask is not None, porosity=wl.s is not None, inplace=inplace)
 
 
 def single_steps(sim, steps: int):
@@ -224,8 +209,8 @@ def thermal_extra(steps: int, warmup: int):
     w, e = timed_steps(sim, steps, warmup)
     alg = algorithmic_bytes(wl, sim.Q, 4)
     sim.close()
-    per = launch_plan(wl, "f32")[1]
-    gbs = alg / (e / steps * per) / 1e9
+    _, per, launches = launch_plan(wl, "f32", steps)
+    gbs = alg / (e / launches) / 1e9
     one = Simulation(wl.lattice, wl.nx, wl.ny, wl.nz, tau=wl.tau, theta=wl.theta, mu=wl.mu, inplace=True)
     one.init(wl.rho, wl.u, wl.thetabar)
     w1, e1 = timed_steps(one, steps, warmup + (warmup % 2))
@@ -243,8 +228,8 @@ def thermal_extra(steps: int, warmup: int):
         s16.init(wl.rho, wl.u, wl.thetabar)
         w16, e16 = timed_steps(s16, steps, warmup + (warmup % 2))
         s16.close()
-        per = launch_plan(wl, "f16", inplace=inplace)[1]
-        g16 = alg16 / (e16 / steps * per) / 1e9
+        _, per, launches = launch_plan(wl, "f16", steps, inplace=inplace)
+        g16 = alg16 / (e16 / launches) / 1e9
         out["f16_inplace" if inplace else "f16"] = {"MLUPS": round(wl.N * steps / w16 / 1e6, 1),
                                                    "ms_per_step": round(w16 / steps * 1e3, 5),
                                                    "achieved_GBs": round(g16, 1), "hbm_frac": round(g16 / 8000.0, 4),
@@ -580,8 +565,8 @@ def main():
     else:
         sim.init(wl.rho, wl.u)
     wall, ev = timed_steps(sim, args.steps, args.warmup)
-    name, per = launch_plan(wl, st, args.rounding, args.inplace)
-    t_launch = ev / args.steps * per
+    name, per, launches = launch_plan(wl, st, args.steps, args.rounding, args.inplace)
+    t_launch = ev / launches
     mlups = N * args.steps / wall / 1e6
     alg = algorithmic_bytes(wl, sim.Q, elem)
     achieved = alg / t_launch / 1e9
@@ -600,12 +585,12 @@ def main():
             s16 = Simulation(wl.lattice, wl.nx, wl.ny, 1, tau=wl.tau, storage=s16s, dev_scale_log2=k, rounding=rnd)
             s16.init(wl.rho)
             w16, e16 = timed_steps(s16, args.steps, args.warmup)
-            t16 = e16 / args.steps
+            _, per16, launches16 = launch_plan(wl, s16s, args.steps, rnd)
             extras[s16s if rnd == "nearest" else s16s + "_stochastic_rounding"] = {
                 "MLUPS": round(N * args.steps / w16 / 1e6, 1),
                 "ms_per_step": round(w16 / args.steps * 1e3, 5),
-                "achieved_GBs": round(bytes_per_node(s16.Q, 2) * N / (t16 * per) / 1e9, 1),
-                "steps_per_launch": per,
+                "achieved_GBs": round(bytes_per_node(s16.Q, 2) * N / (e16 / launches16) / 1e9, 1),
+                "steps_per_launch": per16,
                 "dev_scale_log2": k}
             s16.close()
         extras["adjoint"] = {}
@@ -645,7 +630,8 @@ def main():
         "data": "synthetic",
         "config": {"workload": desc, "lattice": wl.lattice, "nx": wl.nx, "ny": wl.ny, "nz": wl.nz, "storage": st},
         "roofline": {"bound": "hbm" if per == 1 else "latency" if name == "k_march3" else "valu", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic if per == 1 else None, "steps_per_launch": per,
+                     "frac": round(achieved / HBM_PEAK_GBS, 4), "frac_of": "HBM peak, algorithmic bytes per launch",
+                     "traffic": traffic if per == 1 else None, "steps_per_launch": per, "launches": launches,
                      "kernel": name + instance, "bytes_per_launch": alg,
                      "avg_launch_ms": round(t_launch * 1e3, 5)},
     }

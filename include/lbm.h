@@ -95,6 +95,16 @@ enum { LBM_FORCE_SOURCE = 0, LBM_FORCE_SHIFT = 1 };
  * when a reflection would land on one. */
 enum { LBM_SLIP_Y = 1, LBM_SLIP_Z = 2 };
 
+/* Kernels of lbm_step's launches, as lbm_launch_plan reports them (not in the paper). */
+enum {
+    LBM_LAUNCH_SINGLE = 0,  /* one step per launch */
+    LBM_LAUNCH_INPLACE = 1, /* one step per launch, the two phases of the in-place step in turn */
+    LBM_LAUNCH_TILE = 2,    /* D2V9: tiles with halos, steps exchanged through LDS */
+    LBM_LAUNCH_MARCH = 3,   /* D2V9: strips of columns marched along y in registers */
+    LBM_LAUNCH_MARCH3 = 4,  /* D3V19: columns marched along z, planes exchanged through LDS */
+    LBM_LAUNCH_THERMAL = 5  /* D1V7: runs of nodes in registers */
+};
+
 typedef struct {
     int lattice;        /* LBM_D2V9, LBM_D3V19, or LBM_D1V7 (thermal model) */
     int stats;          /* LBM_FERMI_DIRAC or LBM_HERMITE */
@@ -213,6 +223,15 @@ int lbm_init_thermal(lbm_t h, const double *rho, const double *u, const double *
  * between the two in-place kernels; with two, several steps go into one launch where that
  * is faster, with the bits and the state buffer of as many single steps. Async. */
 int lbm_step(lbm_t h, int nsteps);
+
+/* Not in the paper (reporting, e.g. bytes per launch). How lbm_step(h, nsteps) of a handle with
+ * parameters *p launches its steps, nsteps >= 1: the kernel (LBM_LAUNCH_*) and the number of steps of
+ * its first launch, which takes no fewer steps than any other, and the number of launches. solids:
+ * whether a mask is bound (free-slip planes of *p count as solids by themselves); porosity: whether s
+ * is; inplace: whether state_b is NULL. Any output pointer may be NULL. Host only. Errors as
+ * lbm_create, LBM_EINVAL for nsteps < 1. */
+int lbm_launch_plan(const lbm_params *p, int solids, int porosity, int inplace, int nsteps,
+                    int *kernel, int *steps, int *launches);
 
 /* One step of the discrete BGK update of Sec. 9.1 (as lbm_step) from the state in `src`
  * into `dst` (device state buffers of state_bytes,

@@ -287,13 +287,13 @@ void fill_physics(lbm_t h)
     ph.inv_cs2S = (float)(1.0 / (k.cs * k.cs) / (double)ph.scale);
 }
 
-bool has_B(const lbm_t h) { return h->p.B[0] != 0.0 || h->p.B[1] != 0.0 || h->p.B[2] != 0.0; }
-bool has_E(const lbm_t h) { return h->p.E[0] != 0.0 || h->p.E[1] != 0.0 || h->p.E[2] != 0.0; }
+bool has_B(const lbm_params &p) { return p.B[0] != 0.0 || p.B[1] != 0.0 || p.B[2] != 0.0; }
+bool has_E(const lbm_params &p) { return p.E[0] != 0.0 || p.E[1] != 0.0 || p.E[2] != 0.0; }
 // kernel forcing variant: 0 none, 1 source with E, 2 source with E and B, 3 velocity shift
-int force_level(const lbm_t h)
+int force_level(const lbm_params &p)
 {
-    if (h->p.forcing == LBM_FORCE_SHIFT) return (has_E(h) || has_B(h)) ? 3 : 0;
-    return has_B(h) ? 2 : (has_E(h) ? 1 : 0);
+    if (p.forcing == LBM_FORCE_SHIFT) return (has_E(p) || has_B(p)) ? 3 : 0;
+    return has_B(p) ? 2 : (has_E(p) ? 1 : 0);
 }
 // link masks exist where there are solids: obstacles of the mask, or slip wall planes
 bool has_solids(const lbm_t h) { return h->mask != nullptr || h->p.slip != 0; }
@@ -312,29 +312,48 @@ const void *links_of(const lbm_t h) { return has_solids(h) ? h->links : nullptr;
 // neither a source term nor stochastic rounding adds to the VALU's work (FP16 128^3 28 - 30 /
 // 32 - 34; with a source 31 - 36 / 33 - 35, stochastic 256 x 256 x 128 124 - 142 / 114 - 120). The
 // reads of bounced links take 32-bit offsets (FP32 with solids: states below 4 GiB).
-enum MultiStep { kMultiNone, kMultiTile, kMultiMarch, kMultiMarch3 };
-MultiStep multi_step(const lbm_t h)
+struct Route {
+    int kernel;  // LBM_LAUNCH_*
+    int most;    // steps per launch at most
+};
+Route step_route(const lbm_params &p, int N, size_t state_bytes, bool solids, bool soft, bool inplace,
+                 const TilePlan &tile)
 {
-    if (h->aa) return kMultiNone;
-    const size_t bytes = (size_t)h->Q * (size_t)h->stride * h->elem;
-    if (h->p.storage == LBM_F32 && has_solids(h) && bytes >= (1ull << 32)) return kMultiNone;
-    if (h->p.lattice == LBM_D3V19) {
-        if (h->p.storage == LBM_F32) return h->N >= 500000 ? kMultiMarch3 : kMultiNone;
-        if (has_solids(h)) return h->N >= 8000000 ? kMultiMarch3 : kMultiNone;
-        const int force = force_level(h);
-        const bool plain = h->p.rounding == LBM_ROUND_NEAREST && (force == 0 || force == 3);
-        return plain && h->N >= 2000000 ? kMultiMarch3 : kMultiNone;
+    const Route single{LBM_LAUNCH_SINGLE, 1};
+    if (inplace) return {LBM_LAUNCH_INPLACE, 1};
+    if (p.lattice == LBM_D1V7) return {LBM_LAUNCH_THERMAL, kThermalSteps};
+    if (p.storage == LBM_F32 && solids && state_bytes >= (1ull << 32)) return single;
+    const int force = force_level(p);
+    if (p.lattice == LBM_D3V19) {
+        const Route march3{LBM_LAUNCH_MARCH3, 2};
+        if (p.storage == LBM_F32) return N >= 500000 ? march3 : single;
+        if (solids) return N >= 8000000 ? march3 : single;
+        const bool plain = p.rounding == LBM_ROUND_NEAREST && (force == 0 || force == 3);
+        return plain && N >= 2000000 ? march3 : single;
     }
-    if (h->p.lattice != LBM_D2V9) return kMultiNone;
     // The one exception: states in the Infinity Cache without solids, where stochastic rounding, a
     // source term and a porosity field or magnetic term together bound the single step by the
     // VALU too, and tiles repeat that work in their halos (FP16 2048^2 tiles / single steps with E
     // and B 31.9 / 30.5, with E and porosity 33.3 / 31.7, both 35.9 / 32.2).
-    const int force = force_level(h);
-    if (h->p.rounding != LBM_ROUND_NEAREST && !has_solids(h) && (force == 2 || (force == 1 && h->g.s)) &&
-        h->N >= 2000000 && h->N < 6000000)
-        return kMultiNone;
-    return h->N < 8000000 ? kMultiTile : kMultiMarch;
+    if (p.rounding != LBM_ROUND_NEAREST && !solids && (force == 2 || (force == 1 && soft)) && N >= 2000000 &&
+        N < 6000000)
+        return single;
+    if (N < 8000000) return {LBM_LAUNCH_TILE, tile.steps};
+    return {LBM_LAUNCH_MARCH, kMarchSteps};
+}
+Route step_route(const lbm_t h)
+{
+    return step_route(h->p, h->N, (size_t)h->Q * (size_t)h->stride * h->elem, has_solids(h), h->s != nullptr, h->aa,
+                      h->tile);
+}
+// Steps of the next launch where `left` of nsteps are still to go. Launches take an odd number of
+// steps, or, two steps each, come in pairs, so that after any number of steps the state is in the
+// buffer single steps would leave it in (a captured sequence of an even number of steps can be
+// replayed).
+int launch_steps(const Route &r, int nsteps, int left)
+{
+    if (r.kernel == LBM_LAUNCH_MARCH3) return nsteps - left < nsteps / 4 * 4 ? 2 : 1;
+    return std::min(r.most, (left - 1) / 2 * 2 + 1);
 }
 bool adjoint_supported(const lbm_t h) { return !h->thermal; }
 
@@ -643,6 +662,7 @@ int lbm_step(lbm_t h, int nsteps)
     a.links = links_of(h);
     a.remap = use_xcd_remap(h->p.lattice, has_solids(h), h->s != nullptr);
     a.sr = h->p.rounding == LBM_ROUND_STOCHASTIC ? 1 : 0;
+    const Route route = step_route(h);
     if (h->thermal && h->aa) {
         ThermalArgs ta = thermal_args(h);
         ta.src = ta.dst = h->buf[0];
@@ -655,10 +675,9 @@ int lbm_step(lbm_t h, int nsteps)
         return LBM_OK;
     }
     if (h->thermal) {
-        // an odd number of steps per launch, as for the other lattices below
         ThermalArgs ta = thermal_args(h);
         for (int left = nsteps; left > 0;) {
-            const int k = left >= kThermalSteps ? kThermalSteps : (left - 1) / 2 * 2 + 1;
+            const int k = launch_steps(route, nsteps, left);
             ta.src = h->buf[h->cur];
             ta.dst = h->buf[h->cur ^ 1];
             const hipError_t e = k == 1 ? launch_thermal(0, h->p.storage, ta, 0, h->stream)
@@ -670,7 +689,7 @@ int lbm_step(lbm_t h, int nsteps)
         }
         return LBM_OK;
     }
-    const int force = force_level(h);
+    const int force = force_level(h->p);
     if (h->aa) {
         a.src = a.dst = h->buf[0];
         for (int t = 0; t < nsteps; ++t) {
@@ -682,46 +701,48 @@ int lbm_step(lbm_t h, int nsteps)
         }
         return LBM_OK;
     }
-    // Several steps per launch where that is faster; the number of steps of a launch is odd, so
-    // that after any number of steps the state is in the buffer single steps would leave it in
-    // (a captured sequence of an even number of steps can be replayed).
-    int left = nsteps;
-    const MultiStep multi = multi_step(h);
-    const int most = multi == kMultiTile ? h->tile.steps : kMarchSteps;
-    // D3V19: two steps per launch, an even number of launches
-    while (left >= 4 && multi == kMultiMarch3) {
-        for (int i = 0; i < 2; ++i) {
-            const uint32_t keys[2] = {sr_step_key(h->t), sr_step_key(h->t + 1)};
-            a.src = h->buf[h->cur];
-            a.dst = h->buf[h->cur ^ 1];
-            const hipError_t e = launch_march3(h->p.storage, force, a, keys, h->stream);
-            if (e != hipSuccess) return hip_fail(h, e, "multi-step kernel launch");
-            h->cur ^= 1;
-            h->t += 2;
-            left -= 2;
-        }
-    }
-    while (left >= 3 && (multi == kMultiTile || multi == kMultiMarch)) {
-        const int k = left >= most ? most : (left - 1) / 2 * 2 + 1;
+    for (int left = nsteps; left > 0;) {
+        const int k = launch_steps(route, nsteps, left);
         uint32_t keys[kTileSteps];
         for (int i = 0; i < k; ++i) keys[i] = sr_step_key(h->t + (unsigned)i);
         a.src = h->buf[h->cur];
         a.dst = h->buf[h->cur ^ 1];
-        const hipError_t e = multi == kMultiTile ? launch_tile(h->p.storage, force, a, h->tile, k, keys, h->stream)
-                                                 : launch_march(h->p.storage, force, a, k, keys, h->stream);
-        if (e != hipSuccess) return hip_fail(h, e, "multi-step kernel launch");
+        a.sr_key = keys[0];
+        hipError_t e;
+        if (k == 1)
+            e = launch_step(h->p.lattice, h->p.storage, force, a, h->stream);
+        else if (route.kernel == LBM_LAUNCH_TILE)
+            e = launch_tile(h->p.storage, force, a, h->tile, k, keys, h->stream);
+        else if (route.kernel == LBM_LAUNCH_MARCH)
+            e = launch_march(h->p.storage, force, a, k, keys, h->stream);
+        else
+            e = launch_march3(h->p.storage, force, a, keys, h->stream);
+        if (e != hipSuccess) return hip_fail(h, e, k == 1 ? "step kernel launch" : "multi-step kernel launch");
         h->cur ^= 1;
         h->t += (unsigned)k;
         left -= k;
     }
-    for (int t = 0; t < left; ++t) {
-        a.src = h->buf[h->cur];
-        a.dst = h->buf[h->cur ^ 1];
-        a.sr_key = sr_step_key(h->t);
-        const hipError_t e = launch_step(h->p.lattice, h->p.storage, force, a, h->stream);
-        if (e != hipSuccess) return hip_fail(h, e, "step kernel launch");
-        h->cur ^= 1;
-        ++h->t;
+    return LBM_OK;
+}
+
+int lbm_launch_plan(const lbm_params *p, int solids, int porosity, int inplace, int nsteps, int *kernel, int *steps,
+                    int *launches)
+{
+    Sizes sz;
+    const int rc = validate(p, nullptr, &sz);
+    if (rc != LBM_OK) return rc;
+    if (nsteps < 1) return fail(nullptr, LBM_EINVAL, "nsteps must be >= 1");
+    if (p->lattice == LBM_D3V15) return fail(nullptr, LBM_EUNSUPPORTED, "D3V15 has no kernels");
+    if (p->lattice == LBM_D1V7 && (solids || porosity))
+        return fail(nullptr, LBM_EUNSUPPORTED, "D1V7 (thermal model): no solids or porosity");
+    const TilePlan tile = p->lattice == LBM_D2V9 ? tile_plan(p->nx, p->ny) : TilePlan{};
+    const Route r = step_route(*p, sz.N, sz.state, solids || p->slip, porosity != 0, inplace != 0, tile);
+    const int first = launch_steps(r, nsteps, nsteps);
+    if (kernel) *kernel = first > 1 || inplace ? r.kernel : LBM_LAUNCH_SINGLE;
+    if (steps) *steps = first;
+    if (launches) {
+        *launches = 0;
+        for (int left = nsteps; left > 0; left -= launch_steps(r, nsteps, left)) ++*launches;
     }
     return LBM_OK;
 }
@@ -748,7 +769,7 @@ int lbm_step_from(lbm_t h, const void *src, void *dst)
     a.sr_key = sr_step_key(h->t);
     a.src = src;
     a.dst = dst;
-    const hipError_t e = launch_step(h->p.lattice, h->p.storage, force_level(h), a, h->stream);
+    const hipError_t e = launch_step(h->p.lattice, h->p.storage, force_level(h->p), a, h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "step kernel launch");
     ++h->t;
     return LBM_OK;
@@ -1041,7 +1062,7 @@ int lbm_adjoint_step(lbm_t h, const void *state, const float *lam_in, float *lam
     a.grad_s = grad_s;
     a.partials = work_adj(h);
     a.accumulate = h->adj_held ? 1 : 0;
-    hipError_t e = launch_adjoint(h->p.lattice, h->p.storage, has_B(h), h->p.forcing == LBM_FORCE_SHIFT, a, h->stream);
+    hipError_t e = launch_adjoint(h->p.lattice, h->p.storage, has_B(h->p), h->p.forcing == LBM_FORCE_SHIFT, a, h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "adjoint kernel launch");
     h->adj_held = true;
     if (grad_scalars) {

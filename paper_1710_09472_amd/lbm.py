@@ -31,8 +31,13 @@ EXPORTS = [
     "lbm_export_f64", "lbm_set_fields", "lbm_set_tau", "lbm_adjoint_seed", "lbm_adjoint_step",
     "lbm_density_from_mu", "lbm_mu_from_density", "lbm_init_thermal", "lbm_thetabar", "lbm_energy",
     "lbm_speed_change", "lbm_destroy", "lbm_last_error", "lbm_status_string", "lbm_current_noalloc",
-    "lbm_set_step_index",
+    "lbm_set_step_index", "lbm_launch_plan",
 ]
+
+#: Kernels of lbm_step's launches, by LBM_LAUNCH_* (the in-place phases take turns).
+LAUNCH_KERNELS = {"D1V7": {0: "k_thermal_step", 1: "k_thermal_aa_pull+k_thermal_aa_local", 5: "k_thermal_multi"}}
+LAUNCH_KERNELS["D2V9"] = LAUNCH_KERNELS["D3V19"] = {0: "k_step", 1: "k_step_aa_pull+k_step_aa_local", 2: "k_tile",
+                                                    3: "k_march", 4: "k_march3"}
 
 
 class LbmParams(ctypes.Structure):
@@ -89,6 +94,7 @@ def load_library() -> ctypes.CDLL:
         lib.lbm_step.argtypes = [vp, i]
         lib.lbm_step_from.argtypes = [vp, vp, vp]
         lib.lbm_set_step_index.argtypes = [vp, ctypes.c_ulonglong]
+        lib.lbm_launch_plan.argtypes = [P, i, i, i, i] + [ctypes.POINTER(i)] * 3
         lib.lbm_moments.argtypes = [vp, vp, vp]
         lib.lbm_current.argtypes = [vp, ctypes.POINTER(d)]
         lib.lbm_current_noalloc.argtypes = [vp, vp]
@@ -195,6 +201,17 @@ def buffer_sizes(params: LbmParams) -> dict:
     _check(lib.lbm_buffer_sizes(ctypes.byref(params), ctypes.byref(st), ctypes.byref(wk), ctypes.byref(ad),
                                 ctypes.byref(sd)))
     return {"state": st.value, "work": wk.value, "adjoint": ad.value, "stride": sd.value}
+
+
+def launch_plan(params: LbmParams, steps, solids=False, porosity=False, inplace=False):
+    """(kernel, steps of the first and largest launch, number of launches) of Simulation.step(steps)
+    on a grid with these parameters (lbm_launch_plan; no GPU needed)."""
+    lib = load_library()
+    k, per, n = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
+    _check(lib.lbm_launch_plan(ctypes.byref(params), int(bool(solids)), int(bool(porosity)), int(bool(inplace)),
+                               int(steps), ctypes.byref(k), ctypes.byref(per), ctypes.byref(n)))
+    lattice = next(name for name, code in LATTICES.items() if code == params.lattice)
+    return LAUNCH_KERNELS[lattice][k.value], per.value, n.value
 
 
 def _ptr(t):

@@ -8,8 +8,10 @@ import sys
 from pathlib import Path
 
 import numpy as np
+import pytest
 
 import bench
+from paper_1710_09472_amd import lbm
 from paper_1710_09472_amd import workloads as W
 
 ROOT = Path(__file__).resolve().parents[1]
@@ -85,3 +87,29 @@ def test_oracle_blocks_equal_the_full_grid_oracle(oracle_lib):
     # the block of centre (90, 40) holds x = 90..95 and 0..1 (wrapped), y = 40..47
     b = idx[core * core:2 * core * core]
     assert set(b % wl.nx) == set(range(90, 96)) | {0, 1} and set(b // wl.nx) == set(range(40, 48))
+
+
+def test_launch_plan_is_the_librarys():
+    """The kernel and launch counts of a bench line are the library's own plan: remainder launches
+    count (4096 x 4: 17 + 3 of 20 steps), and FP32 states of 4 GiB with solids take single steps."""
+    wl = W.throughput_2d(nx=4096, ny=4)
+    assert bench.launch_plan(wl, "f32", 20) == ("k_tile", 17, 2)
+    assert bench.launch_plan(wl, "f32", 20, inplace=True) == ("k_step_aa_pull+k_step_aa_local", 1, 20)
+    wl = W.throughput_2d(nx=16, ny=16)
+    wl.nx, wl.ny = 12000, 10000  # (the plan takes the sizes alone)
+    assert bench.launch_plan(wl, "f32", 20) == ("k_march", 5, 4)
+    wl.mask = np.zeros(1, np.uint8)
+    assert bench.launch_plan(wl, "f32", 20) == ("k_step", 1, 20)
+    assert bench.launch_plan(wl, "f16", 21, "stochastic") == ("k_march", 5, 5)  # 4 of 5 steps, one of 1
+
+
+def test_launch_plan_launches_and_errors():
+    p3 = lbm.make_params("D3V19", 128, 128, 128)
+    assert lbm.launch_plan(p3, 3) == ("k_step", 1, 3)  # launches of two steps come in pairs
+    assert lbm.launch_plan(p3, 11) == ("k_march3", 2, 7)
+    pt = lbm.make_params("D1V7", 1000, theta=0.25)
+    assert [lbm.launch_plan(pt, n) for n in (1, 2, 9)] == [("k_thermal_step", 1, 1), ("k_thermal_step", 1, 2),
+                                                         ("k_thermal_multi", 5, 3)]  # 5 + 3 + 1
+    for bad in ((p3, 0, {}), (lbm.make_params("D2V9", 8, 8, tau=0.5), 1, {}), (pt, 1, {"solids": True})):
+        with pytest.raises(lbm.LbmError):
+            lbm.launch_plan(bad[0], bad[1], **bad[2])
