@@ -49,7 +49,9 @@ struct lbm_s {
     bool adj_held = false;  // work_adj holds adjoint contributions not yet reduced
     bool thermal = false;   // D1V7: the fourth-order thermal model
     ThermalPhysics tph{};
-    TilePlan tile{};        // small D2V9 grids: tiles of the multi-step launches
+    int cus = 0;            // compute units of the handle's device
+    TilePlan tile{};        // D2V9: tiles of the multi-step launches
+    March3Plan march3{};    // D3V19: blocks of the two-step launches
     std::string err;
 };
 
@@ -355,6 +357,17 @@ int launch_steps(const Route &r, int nsteps, int left)
     if (r.kernel == LBM_LAUNCH_MARCH3) return nsteps - left < nsteps / 4 * 4 ? 2 : 1;
     return std::min(r.most, (left - 1) / 2 * 2 + 1);
 }
+// Compute units of the stream's device (NULL: the current one), by which the multi-step launches
+// are planned; without a device the 256 of an MI355X.
+int device_cus(hipStream_t stream)
+{
+    int dev = 0, cus = 0;
+    hipError_t e = stream ? hipStreamGetDevice(stream, &dev) : hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess && cus > 0) return cus;
+    (void)hipGetLastError();  // (not the error of a later launch)
+    return 256;
+}
 bool adjoint_supported(const lbm_t h) { return !h->thermal; }
 
 // Constants of the thermal kernel (D1V7) from the weights: what, xi, the weight's
@@ -567,7 +580,9 @@ int lbm_create(const lbm_params *p, const uint8_t *mask, const float *s, void *s
     h->g.s = s;
     h->g.slip = p->slip;
     h->thermal = p->lattice == LBM_D1V7;
-    if (p->lattice == LBM_D2V9) h->tile = tile_plan(p->nx, p->ny);
+    h->cus = device_cus(h->stream);
+    if (p->lattice == LBM_D2V9) h->tile = tile_plan(p->nx, p->ny, h->cus);
+    if (p->lattice == LBM_D3V19) h->march3 = march3_plan(p->nx, p->ny, p->nz, h->cus);
     if (h->thermal)
         fill_thermal(h);
     else
@@ -714,9 +729,9 @@ int lbm_step(lbm_t h, int nsteps)
         else if (route.kernel == LBM_LAUNCH_TILE)
             e = launch_tile(h->p.storage, force, a, h->tile, k, keys, h->stream);
         else if (route.kernel == LBM_LAUNCH_MARCH)
-            e = launch_march(h->p.storage, force, a, k, keys, h->stream);
+            e = launch_march(h->p.storage, force, a, h->cus, k, keys, h->stream);
         else
-            e = launch_march3(h->p.storage, force, a, keys, h->stream);
+            e = launch_march3(h->p.storage, force, a, h->march3, keys, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, k == 1 ? "step kernel launch" : "multi-step kernel launch");
         h->cur ^= 1;
         h->t += (unsigned)k;
@@ -735,7 +750,7 @@ int lbm_launch_plan(const lbm_params *p, int solids, int porosity, int inplace, 
     if (p->lattice == LBM_D3V15) return fail(nullptr, LBM_EUNSUPPORTED, "D3V15 has no kernels");
     if (p->lattice == LBM_D1V7 && (solids || porosity))
         return fail(nullptr, LBM_EUNSUPPORTED, "D1V7 (thermal model): no solids or porosity");
-    const TilePlan tile = p->lattice == LBM_D2V9 ? tile_plan(p->nx, p->ny) : TilePlan{};
+    const TilePlan tile = p->lattice == LBM_D2V9 ? tile_plan(p->nx, p->ny, device_cus(nullptr)) : TilePlan{};
     const Route r = step_route(*p, sz.N, sz.state, solids || p->slip, porosity != 0, inplace != 0, tile);
     const int first = launch_steps(r, nsteps, nsteps);
     if (kernel) *kernel = first > 1 || inplace ? r.kernel : LBM_LAUNCH_SINGLE;

@@ -198,26 +198,38 @@ hipError_t launch_step(int lattice, int storage, int force, const StepArgs &a, h
 // the same with stochastic rounding (16-bit storage; a.sr set)
 hipError_t launch_step_sr(int lattice, int storage, int force, const StepArgs &a, hipStream_t st);
 // Several D2V9 steps in one launch, two state buffers (lbm_march.hip): `steps` (3 or 5) time
-// steps from a.src into a.dst, the same bits as single steps; keys: the sr_key of each.
+// steps from a.src into a.dst, the same bits as single steps; keys: the sr_key of each; cus: the
+// device's compute units.
 constexpr int kMarchSteps = 5;  // steps per launch at most
-hipError_t launch_march(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st);
-hipError_t launch_march_16(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st);
-hipError_t launch_march_sr(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st);
+hipError_t launch_march(int storage, int force, const StepArgs &a, int cus, int steps, const uint32_t *keys,
+                        hipStream_t st);
+hipError_t launch_march_16(int storage, int force, const StepArgs &a, int cus, int steps, const uint32_t *keys,
+                           hipStream_t st);
+hipError_t launch_march_sr(int storage, int force, const StepArgs &a, int cus, int steps, const uint32_t *keys,
+                           hipStream_t st);
 // Two D3V19 steps in one launch, two state buffers (lbm_march3.hip), the same bits as single steps.
-hipError_t launch_march3(int storage, int force, const StepArgs &a, const uint32_t *keys, hipStream_t st);
-hipError_t launch_march3_f16(int force, const StepArgs &a, const uint32_t *keys, hipStream_t st);
-hipError_t launch_march3_f16_sr(int force, const StepArgs &a, const uint32_t *keys, hipStream_t st);
-hipError_t launch_march3_bf16(int force, const StepArgs &a, const uint32_t *keys, hipStream_t st);
-hipError_t launch_march3_bf16_sr(int force, const StepArgs &a, const uint32_t *keys, hipStream_t st);
+struct March3Plan {
+    int ntx, nty;  // columns of blocks along x and y
+    int planes;    // planes a block writes
+};
+March3Plan march3_plan(int nx, int ny, int nz, int cus);
+hipError_t launch_march3(int storage, int force, const StepArgs &a, const March3Plan &p, const uint32_t *keys,
+                         hipStream_t st);
+hipError_t launch_march3_f16(int force, const StepArgs &a, const March3Plan &p, const uint32_t *keys, hipStream_t st);
+hipError_t launch_march3_f16_sr(int force, const StepArgs &a, const March3Plan &p, const uint32_t *keys,
+                                hipStream_t st);
+hipError_t launch_march3_bf16(int force, const StepArgs &a, const March3Plan &p, const uint32_t *keys, hipStream_t st);
+hipError_t launch_march3_bf16_sr(int force, const StepArgs &a, const March3Plan &p, const uint32_t *keys,
+                                 hipStream_t st);
 // The same on small grids by tiles (lbm_tile.hip): 1 .. p.steps steps in one launch.
 struct TilePlan {
-    int steps;     // most steps per launch (odd), 0: not for this grid
+    int steps;     // most steps per launch (odd)
     int tx, ty;    // nodes a block writes
     int ntx, nty;  // tiles along x and y
 };
 constexpr int kTileThreads = 1024;  // threads per block at most
 constexpr int kTileSteps = 17;      // steps per launch at most
-TilePlan tile_plan(int nx, int ny);
+TilePlan tile_plan(int nx, int ny, int cus);
 hipError_t launch_tile(int storage, int force, const StepArgs &a, const TilePlan &p, int steps, const uint32_t *keys,
                        hipStream_t st);
 hipError_t launch_tile_16(int storage, int force, const StepArgs &a, const TilePlan &p, int steps,

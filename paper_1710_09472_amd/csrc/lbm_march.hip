@@ -4,11 +4,12 @@
 
 namespace lbm {
 
-hipError_t launch_march(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st)
+hipError_t launch_march(int storage, int force, const StepArgs &a, int cus, int steps, const uint32_t *keys,
+                        hipStream_t st)
 {
     if (steps != 3 && steps != kMarchSteps) return hipErrorInvalidValue;
-    if (storage == LBM_F32) return march_st<LBM_F32, false>(force, a, steps, keys, st);
-    return launch_march_16(storage, force, a, steps, keys, st);
+    if (storage == LBM_F32) return march_st<LBM_F32, false>(force, a, cus, steps, keys, st);
+    return launch_march_16(storage, force, a, cus, steps, keys, st);
 }
 
 }  // namespace lbm

@@ -4,11 +4,29 @@
 
 namespace lbm {
 
-hipError_t launch_march3(int storage, int force, const StepArgs &a, const uint32_t *keys, hipStream_t st)
+// Planes per segment: the grid's columns of blocks times the segments fill the CUs (one block
+// each) in as few rounds of as few planes (two of them recomputed) as there are.
+March3Plan march3_plan(int nx, int ny, int nz, int cus)
 {
-    if (storage == LBM_F32) return march3_st<LBM_F32, false>(force, a, keys, st);
-    if (storage == LBM_F16) return launch_march3_f16(force, a, keys, st);
-    if (storage == LBM_BF16) return launch_march3_bf16(force, a, keys, st);
+    March3Plan p{(nx + kM3Cols - 1) / kM3Cols, (ny + kM3Rows - 3) / (kM3Rows - 2), nz};
+    const long long columns = (long long)p.ntx * p.nty;
+    long long cost = 1ll << 60;
+    for (int nseg = 1; nseg <= std::max(1, nz / 4); ++nseg) {
+        const int planes = (nz + nseg - 1) / nseg, used = (nz + planes - 1) / planes;
+        const long long c = (columns * used + cus - 1) / cus * (planes + 3);
+        if (c < cost) {
+            cost = c;
+            p.planes = planes;
+        }
+    }
+    return p;
+}
+
+hipError_t launch_march3(int storage, int force, const StepArgs &a, const March3Plan &p, const uint32_t *keys, hipStream_t st)
+{
+    if (storage == LBM_F32) return march3_st<LBM_F32, false>(force, a, p, keys, st);
+    if (storage == LBM_F16) return launch_march3_f16(force, a, p, keys, st);
+    if (storage == LBM_BF16) return launch_march3_bf16(force, a, p, keys, st);
     return hipErrorInvalidValue;
 }
 

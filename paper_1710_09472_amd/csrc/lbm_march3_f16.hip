@@ -4,10 +4,10 @@
 
 namespace lbm {
 
-hipError_t launch_march3_f16(int force, const StepArgs &a, const uint32_t *keys, hipStream_t st)
+hipError_t launch_march3_f16(int force, const StepArgs &a, const March3Plan &p, const uint32_t *keys, hipStream_t st)
 {
-    if (a.sr) return launch_march3_f16_sr(force, a, keys, st);
-    return march3_st<LBM_F16, false>(force, a, keys, st);
+    if (a.sr) return launch_march3_f16_sr(force, a, p, keys, st);
+    return march3_st<LBM_F16, false>(force, a, p, keys, st);
 }
 
 }  // namespace lbm

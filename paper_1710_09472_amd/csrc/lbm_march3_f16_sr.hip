@@ -4,9 +4,9 @@
 
 namespace lbm {
 
-hipError_t launch_march3_f16_sr(int force, const StepArgs &a, const uint32_t *keys, hipStream_t st)
+hipError_t launch_march3_f16_sr(int force, const StepArgs &a, const March3Plan &p, const uint32_t *keys, hipStream_t st)
 {
-    return march3_st<LBM_F16, true>(force, a, keys, st);
+    return march3_st<LBM_F16, true>(force, a, p, keys, st);
 }
 
 }  // namespace lbm

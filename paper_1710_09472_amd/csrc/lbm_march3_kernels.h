@@ -30,7 +30,6 @@ namespace {
 
 constexpr int kM3Rows = 15, kM3Cols = 64;        // rows and columns a block holds in its row waves
 constexpr int kM3Threads = 64 * (kM3Rows + 1);
-constexpr int kM3Resident = 256 * (1024 / kM3Threads);  // blocks the 256 CUs hold
 constexpr int kM3Stride = kM3Cols + 2;           // LDS row: the columns and one on each side
 constexpr int kM3Plane = kM3Rows * kM3Stride;
 
@@ -258,33 +257,16 @@ __global__ __launch_bounds__(kM3Threads, 4) void k_march3(March3Args ma)
     }
 }
 
-// Planes per segment: the grid's columns of blocks times the segments fill the 256 CUs (one
-// block each) in as few rounds of as few planes (two of them recomputed) as there are.
-inline int march3_planes(int columns, int nz)
-{
-    int best = nz;
-    long long cost = 1ll << 60;
-    for (int nseg = 1; nseg <= std::max(1, nz / 4); ++nseg) {
-        const int planes = (nz + nseg - 1) / nseg, used = (nz + planes - 1) / planes;
-        const long long c = ((long long)columns * used + kM3Resident - 1) / kM3Resident * (planes + 3);
-        if (c < cost) {
-            cost = c;
-            best = planes;
-        }
-    }
-    return best;
-}
-
 // Two time steps from a.src into a.dst with the step keys `keys`.
 template <int ST, bool SR>
-hipError_t march3_st(int force, const StepArgs &a, const uint32_t *keys, hipStream_t st)
+hipError_t march3_st(int force, const StepArgs &a, const March3Plan &p, const uint32_t *keys, hipStream_t st)
 {
     const bool mask = a.links != nullptr, soft = a.g.s != nullptr, slip = a.g.slip != 0;
     March3Args ma{};
     ma.a = a;
-    ma.ntx = (a.g.nx + kM3Cols - 1) / kM3Cols;
-    ma.nty = (a.g.ny + kM3Rows - 3) / (kM3Rows - 2);
-    ma.planes = march3_planes(ma.ntx * ma.nty, a.g.nz);
+    ma.ntx = p.ntx;
+    ma.nty = p.nty;
+    ma.planes = p.planes;
     ma.div_ntx = make_fastdiv(ma.ntx);
     ma.div_nty = make_fastdiv(ma.nty);
     ma.key[0] = keys[0];

@@ -263,29 +263,25 @@ __global__ __launch_bounds__(kMarchBlock, 4) void k_march(MarchArgs ma)
 // least 16 rows, below which the recomputed ones weigh more than idle CUs (FP32 1531 x 1117
 // disks: 16 rows 12.8 us per step, 8 rows 13.3 us, 24 rows 16.9 us).
 template <class Kernel>
-int march_rows(Kernel kernel, int nbx, int ny)
+int march_rows(Kernel kernel, int nbx, int ny, int cus)
 {
-    static const int resident = [&] {
-        int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kMarchBlock, 0) != hipSuccess || per_cu < 1)
-            per_cu = 4;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-            cus = 256;
-        return std::max(1, per_cu - 1) * cus;
+    static const int per_cu = [&] {  // a property of the kernel, the same on every gfx950
+        int n = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, kMarchBlock, 0) != hipSuccess || n < 1) n = 4;
+        return std::max(1, n - 1);
     }();
-    const int segs = std::max(1, resident / nbx);
+    const int segs = std::max(1, per_cu * cus / nbx);
     return std::max(16, (ny + segs - 1) / segs);
 }
 
 template <int ST, bool MASK, bool SOFT, int FORCE, bool SLIP, bool SR>
-hipError_t march_launch(MarchArgs &ma, hipStream_t st)
+hipError_t march_launch(MarchArgs &ma, int cus, hipStream_t st)
 {
     constexpr int W = kMarchWidth * (kMarchBlock / 64);
     const Geometry &g = ma.a.g;
     const auto kernel = k_march<ST, MASK, SOFT, FORCE, SLIP, SR>;
     ma.nbx = (g.nx + W - 1) / W;
-    ma.rows = march_rows(kernel, ma.nbx, g.ny);
+    ma.rows = march_rows(kernel, ma.nbx, g.ny, cus);
     ma.div_nbx = make_fastdiv(ma.nbx);
     const int nseg = (g.ny + ma.rows - 1) / ma.rows;
     hipLaunchKernelGGL(kernel, dim3(ma.nbx * nseg), dim3(kMarchBlock), 0, st, ma);
@@ -294,7 +290,7 @@ hipError_t march_launch(MarchArgs &ma, hipStream_t st)
 
 // `steps` time steps (3 or 5) from a.src into a.dst with the step keys `keys`.
 template <int ST, bool SR>
-hipError_t march_st(int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st)
+hipError_t march_st(int force, const StepArgs &a, int cus, int steps, const uint32_t *keys, hipStream_t st)
 {
     const bool mask = a.links != nullptr, soft = a.g.s != nullptr, slip = a.g.slip != 0;
     MarchArgs ma{};
@@ -302,7 +298,7 @@ hipError_t march_st(int force, const StepArgs &a, int steps, const uint32_t *key
     ma.steps = steps;
     for (int k = 0; k < steps; ++k) ma.keys[k] = ma.last_key = keys[k];
 #define LBM_MARCH(M, S, F) \
-    return M && slip ? march_launch<ST, M, S, F, M, SR>(ma, st) : march_launch<ST, M, S, F, false, SR>(ma, st)
+    return M && slip ? march_launch<ST, M, S, F, M, SR>(ma, cus, st) : march_launch<ST, M, S, F, false, SR>(ma, cus, st)
 #define LBM_MARCH_F(M, S)                   \
     do {                                    \
         if (force == 0) LBM_MARCH(M, S, 0); \

@@ -4,10 +4,11 @@
 
 namespace lbm {
 
-hipError_t launch_march_sr(int storage, int force, const StepArgs &a, int steps, const uint32_t *keys, hipStream_t st)
+hipError_t launch_march_sr(int storage, int force, const StepArgs &a, int cus, int steps, const uint32_t *keys,
+                           hipStream_t st)
 {
-    if (storage == LBM_F16) return march_st<LBM_F16, true>(force, a, steps, keys, st);
-    if (storage == LBM_BF16) return march_st<LBM_BF16, true>(force, a, steps, keys, st);
+    if (storage == LBM_F16) return march_st<LBM_F16, true>(force, a, cus, steps, keys, st);
+    if (storage == LBM_BF16) return march_st<LBM_BF16, true>(force, a, cus, steps, keys, st);
     return hipErrorInvalidValue;
 }
 

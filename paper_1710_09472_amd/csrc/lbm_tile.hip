@@ -6,7 +6,7 @@
 
 namespace lbm {
 
-// Tiles by measurement: the most steps whose tiles fit the 256 CUs once (a second block per CU
+// Tiles by measurement: the most steps whose tiles fit the CUs (256) once (a second block per CU
 // takes turns with the first), on the smallest tiles that do (fewer wavefronts per SIMD). us per
 // step, FP32 with solids:
 //   64 x 32    4 x 4, 9 steps 0.76    8 x 8, 9 steps 0.86    16 x 16, 9 steps 1.04
@@ -19,14 +19,14 @@ namespace lbm {
 //   2048^2     24 x 24, 5 steps 23.2  32 x 16, 5 steps 29.3  56 x 8, 5 steps 25.4
 // Grids of few rows (columns): the tile spans them, so that only the long axis has a halo and
 // more steps fit (4096 x 4: 32 columns, 17 steps 0.54; 9 steps 0.68).
-TilePlan tile_plan(int nx, int ny)
+TilePlan tile_plan(int nx, int ny, int cus)
 {
     TilePlan p{};
     auto fits = [&](int steps, int tx, int ty) {
         p.steps = steps;
         p.tx = tx;
         p.ty = ty;
-        return (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) <= 256;
+        return (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) <= cus;
     };
     if (std::min(nx, ny) <= 8 && std::max(nx, ny) > 64) {
         if (nx <= ny)
