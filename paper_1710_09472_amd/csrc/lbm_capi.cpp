@@ -340,7 +340,14 @@ Route step_route(const lbm_params &p, int N, size_t state_bytes, bool solids, bo
     if (p.rounding != LBM_ROUND_NEAREST && !solids && (force == 2 || (force == 1 && soft)) && N >= 2000000 &&
         N < 6000000)
         return single;
-    if (N < 8000000) return {LBM_LAUNCH_TILE, tile.steps};
+    // Grids that leave strips idle stay on tiles at any size: a strip needs its 64 lanes and rows to
+    // walk. us per step, strips / tiles / single steps, FP32 without solids: 9 10^6 x 1
+    // 114 / 22 / 106, 4.5 10^6 x 2 76 / 22 / 106, 1.1 10^6 x 8 41 / 26 / 127, 12 columns 197 / 48 /
+    // 388, 64 columns 57 / 45 / 117, 100 columns 41 / 49 / 160; BF16 with solids, stochastic: 64
+    // columns 130 / 70 / 119, 100 columns 84 / 76 / 105. (Tiles take 32-bit byte offsets.)
+    const bool thin = p.nx < 100 || p.ny <= 8;
+    if (thin && state_bytes >= (1ull << 32)) return single;
+    if (thin || N < 8000000) return {LBM_LAUNCH_TILE, tile.steps};
     return {LBM_LAUNCH_MARCH, kMarchSteps};
 }
 Route step_route(const lbm_t h)

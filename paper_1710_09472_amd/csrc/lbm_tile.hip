@@ -18,7 +18,13 @@ namespace lbm {
 //   512 x 512  24 x 24, 5 steps 2.21  32 x 16, 5 steps 2.38  28 x 28, 3 steps 2.91
 //   2048^2     24 x 24, 5 steps 23.2  32 x 16, 5 steps 29.3  56 x 8, 5 steps 25.4
 // Grids of few rows (columns): the tile spans them, so that only the long axis has a halo and
-// more steps fit (4096 x 4: 32 columns, 17 steps 0.54; 9 steps 0.68).
+// more steps fit (4096 x 4: 32 columns, 17 steps 0.54; 9 steps 0.68). Along that axis it is as
+// long as one tile per CU makes it, between 32 nodes and a block of 1024 threads: a block holds
+// 64 KB of LDS whatever its threads, so many short tiles leave the CUs with a wave or two each.
+// us per step, FP32 without solids, tiles of 32 / as planned / single steps: 40000 x 1
+// 1.06 / 0.52 / 3.4, 400000 x 2 8.5 / 2.7 / 12.4, 400000 x 8 14.6 / 9.6 / 40, 4 10^6 x 1
+// 75 / 9.9 / 50; BF16 with solids, stochastic: 500000 x 2 19.3 / 5.1 / 14.0, 4 10^6 x 1
+// 121 / 16.2 / 34.
 TilePlan tile_plan(int nx, int ny, int cus)
 {
     TilePlan p{};
@@ -28,11 +34,13 @@ TilePlan tile_plan(int nx, int ny, int cus)
         p.ty = ty;
         return (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) <= cus;
     };
-    if (std::min(nx, ny) <= 8 && std::max(nx, ny) > 64) {
+    const int narrow = std::min(nx, ny), wide = std::max(nx, ny);
+    if (narrow <= 8 && wide > 64) {
+        const int len = std::min(std::max(((wide + cus - 1) / cus + 31) / 32 * 32, 32), kTileThreads / narrow - 32);
         if (nx <= ny)
-            fits(17, nx, 32);
+            fits(17, nx, len);
         else
-            fits(17, 32, ny);
+            fits(17, len, ny);
     } else if (!fits(9, 4, 4) && !fits(9, 8, 8) && !fits(9, 16, 16) && !fits(7, 20, 18)) {
         fits(5, 24, 24);
     }

@@ -113,3 +113,19 @@ def test_launch_plan_launches_and_errors():
     for bad in ((p3, 0, {}), (lbm.make_params("D2V9", 8, 8, tau=0.5), 1, {}), (pt, 1, {"solids": True})):
         with pytest.raises(lbm.LbmError):
             lbm.launch_plan(bad[0], bad[1], **bad[2])
+
+
+def test_thin_grids_are_planned_by_their_shape():
+    """Strips write 56 of 64 columns and walk rows, so grids of few columns or rows take tiles at any
+    size (FP32 states of 4 GiB and more single steps, the tiles' offsets being 32 bits wide)."""
+    def plan(nx, ny, **kw):
+        return lbm.launch_plan(lbm.make_params("D2V9", nx, ny, **kw), 34)
+
+    for nx, ny in ((9_000_000, 1), (4_500_000, 2), (1_200_000, 8), (1, 9_000_000), (4, 2_250_000), (8, 1_125_000)):
+        assert plan(nx, ny) == ("k_tile", 17, 2), (nx, ny)
+    for nx, ny in ((9, 1_000_000), (64, 140_625), (99, 90_000)):
+        assert plan(nx, ny)[:2] == ("k_tile", 5), (nx, ny)
+    for nx, ny in ((100, 90_000), (1_000_000, 9), (4096, 4096)):
+        assert plan(nx, ny)[:2] == ("k_march", 5), (nx, ny)
+    assert plan(120_000_000, 1) == plan(1, 120_000_000) == ("k_step", 1, 34)
+    assert plan(120_000_000, 1, storage="bf16") == ("k_tile", 17, 2)

@@ -71,6 +71,20 @@ def test_same_bits_on_larger_strips_and_each_plan(nx, ny, storage, rounding, kin
     assert torch.equal(one.export_f64(), many.export_f64(many.bufs[0]))
 
 
+# thin grids: tiles that span the short axis, of 32 nodes (256 and 257 of them along the long axis), longer
+# ones and the longest a block holds, below and beyond 8 M nodes; few columns beyond 8 M nodes
+@pytest.mark.parametrize("kind", ["open", "walls", "soft", "slip"])
+@pytest.mark.parametrize("storage,rounding", [("f32", "nearest"), ("f16", "nearest"), ("bf16", "stochastic")])
+@pytest.mark.parametrize("nx,ny", [(8192, 1), (8193, 1), (3, 8193), (300001, 1), (1, 300001), (40001, 3), (6, 40001),
+                                   (20011, 7), (8, 99999), (8000003, 1), (4, 2000003), (1000003, 8), (99, 80809)])
+def test_same_bits_on_thin_grids(nx, ny, storage, rounding, kind):
+    one, many = (_sim(nx, ny, storage, rounding, kind) for _ in range(2))
+    for _ in range(22):
+        one.step(1)
+    many.step(22)  # 17 + 5, or 5 + 5 + 5 + 5 + 1 + 1
+    assert torch.equal(one.export_f64(), many.export_f64(many.bufs[0]))
+
+
 @pytest.mark.parametrize("nx,ny", [(300, 290), (1120, 600)])
 def test_captured_steps_replay(nx, ny):
     """A graph of an even number of steps advances the state on every replay."""
