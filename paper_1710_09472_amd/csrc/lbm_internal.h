@@ -211,6 +211,8 @@ hipError_t launch_march_sr(int storage, int force, const StepArgs &a, int cus, i
 struct March3Plan {
     int ntx, nty;  // columns of blocks along x and y
     int planes;    // planes a block writes
+    float slots;   // lanes times planes the CUs spend on one node
+    float lanes;   // lanes the single step spends on one node of a row
 };
 March3Plan march3_plan(int nx, int ny, int nz, int cus);
 hipError_t launch_march3(int storage, int force, const StepArgs &a, const March3Plan &p, const uint32_t *keys,

@@ -129,3 +129,26 @@ def test_thin_grids_are_planned_by_their_shape():
         assert plan(nx, ny)[:2] == ("k_march", 5), (nx, ny)
     assert plan(120_000_000, 1) == plan(1, 120_000_000) == ("k_step", 1, 34)
     assert plan(120_000_000, 1, storage="bf16") == ("k_tile", 17, 2)
+
+
+def test_two_step_launches_of_3d_grids_are_planned_by_their_shape():
+    """k_march3 pays for whole blocks of 64 x 13 columns: narrow and flat grids, on which it measured
+    slower than single steps, keep those; the grids it gains on keep it."""
+    def kernel(nx, ny, nz, solids=False, porosity=False, **kw):
+        return lbm.launch_plan(lbm.make_params("D3V19", nx, ny, nz, **kw), 8, solids, porosity)[0]
+
+    E, bf16 = {"E": (1e-6, 0, 0)}, {"storage": "bf16"}
+    for dims in ((512, 512, 2), (1024, 512, 1), (4096, 2048, 1), (8, 256, 256), (1, 1000, 520)):
+        assert kernel(*dims) == kernel(*dims, solids=True) == kernel(*dims, solids=True, porosity=True) == "k_step"
+    for dims in ((256, 128, 16), (32, 128, 128)):  # even or faster without solids only
+        assert (kernel(*dims, **E), kernel(*dims, solids=True, **E)) == ("k_march3", "k_step")
+    # solids with porosity: the instances that spill lose from about two slots per node
+    assert kernel(256, 16, 2048, True, True) == kernel(96, 96, 96, True, True) == "k_step"
+    assert kernel(256, 16, 2048, True, True, **E) == kernel(96, 96, 96, True, True, **E) == "k_march3"
+    for dims in ((1024, 1024, 8), (512, 512, 32), (256, 16, 2048), (32, 512, 512)):
+        assert kernel(*dims, **bf16) == "k_step"
+    assert kernel(2048, 1024, 4, True, True, slip=lbm.SLIP_Y, **bf16) == "k_step"
+    for dims in ((128, 128, 128), (256, 128, 128), (96, 96, 96), (65, 128, 128), (24, 160, 160)):
+        assert kernel(*dims, **E) == "k_march3"
+    assert kernel(256, 128, 128, True, E=(1e-6, 0, 0), B=(0, 0, 1e-3)) == kernel(128, 128, 128, True, True) == "k_march3"
+    assert kernel(128, 256, 256, **bf16) == kernel(128, 256, 256, True, True, **bf16) == "k_march3"
