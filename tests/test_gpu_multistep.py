@@ -10,7 +10,8 @@ from paper_1710_09472_amd import lbm
 
 pytestmark = pytest.mark.gpu
 
-# nx, ny: tiles (one block, ragged tiles, thin grids), larger grids of odd shapes
+# nx, ny: tiles (one block, ragged tiles, thin grids), larger grids of odd shapes (below 8 M nodes tiles
+# as well; the strips' grids follow further down)
 TILES = [(1, 1), (5, 3), (16, 16), (33, 18), (70, 9), (300, 5), (4, 131), (301, 290), (1000, 640)]
 STRIPS = [(56, 24000), (223, 5900), (225, 5861), (1120, 1171), (65537, 21), (350000, 4)]
 
@@ -147,8 +148,10 @@ def _sim3(nx, ny, nz, storage, rounding, kind):
     return sim
 
 
-# grids on which two steps share a launch (FP32: N >= 500000; 16 bits: N >= 2 M without solids and source
-# term, N >= 8 M with solids): widths around a block's 64 columns, heights around its 13 rows, thin axes
+# 3D grids from the sizes at which two steps may share a launch (FP32: N >= 500000; 16 bits: N >= 2 M without
+# solids and source term, N >= 8 M with solids): widths around a block's 64 columns, heights around its 13
+# rows, thin axes (the thinnest are planned for single steps; test_gpu_multistep_instances.py asserts the
+# kernel it runs)
 LARGE3 = [(65, 14, 551), (63, 100, 80), (130, 27, 143), (3, 410, 409), (1, 1000, 501), (700, 751, 1), (1024, 2, 250),
           (250, 13, 155), (64, 26, 301)]
 
