@@ -327,13 +327,33 @@ hipError_t aa_v(int force, int phase, const StepArgs &a, hipStream_t st)
 
 // The local phase without solids reads and writes every node at its own slots and nowhere
 // else, so its tiles need not follow the rows: as one row of N nodes every block starts on a
-// cache line whatever nx is. (Measured on MI355X, BF16 4000 x 3001, where every second row
-// starts in mid-line: 108.5 us per phase by rows, 63.9 us as one row.)
+// cache line and fills its waves whatever nx is. That pays where rows start in mid-line (BF16
+// 4000 x 3001 108.5 us per phase by rows, 63.9 us as one row). By rows, on the other hand, the
+// blocks meet the nodes that the pull phase left in the L2 of their XCD, which counts as long as the
+// state stays in the L2s and the blocks are in the hardware's order (remap 0; in slabs per XCD both
+// ways meet them), unless rows leave many lanes idle; and tiny grids, all latency, want many small
+// blocks. us per step of two phases, by rows / as one row: FP32 500^2 6.6 / 7.1, FP16 768 x 1000
+// 8.2 / 9.9, 1000^2 10.8 / 11.2, FP32 1000^2 (36 MB) 15.6 / 14.3; FP32 100^3 34.3 / 28.2; idle lanes:
+// FP16 101 x 3001 7.2 / 6.4, 2 x 400000 160 / 93; FP16 32^2 with porosity 3.2 / 3.5.
+template <int ST>
+bool local_phase_as_one_row(int N, int nx, int V, size_t state_bytes, int remap)
+{
+    const bool beyond_l2 = state_bytes >= (20u << 20);
+    // (in the L2s half lines do as well: FP16 96 x 3000 with porosity 4.7 / 4.9)
+    const unsigned line = beyond_l2 ? 128 : 64, row = (unsigned)nx * sizeof(typename Codec<ST>::T);
+    if (N < 50000 || row % line == 0) return false;
+    const int lanes = (nx / V + 63) / 64 * 64;  // of a row's waves
+    return remap == 1 || beyond_l2 || lanes * V * 4 >= nx * 5;
+}
+
 template <int LAT, int ST, bool SR>
 hipError_t aa_lat_st(int force, int phase, const StepArgs &a0, hipStream_t st)
 {
     StepArgs a = a0;
-    if (phase == 1 && !a.links) {
+    const size_t state_bytes = (size_t)Lat<LAT>::Q * (size_t)a.g.stride * sizeof(typename Codec<ST>::T);
+    if (phase == 1 && !a.links &&
+        local_phase_as_one_row<ST>(a.g.nx * a.g.ny * a.g.nz, a.g.nx, step_vector_width(LAT, ST, a.g.nx, false), state_bytes,
+                                   a.remap)) {
         a.g.nx = a.g.nx * a.g.ny * a.g.nz;
         a.g.ny = a.g.nz = 1;
         a.g.div_ny = make_fastdiv(1);

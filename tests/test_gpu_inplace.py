@@ -165,3 +165,23 @@ def test_inplace_full_size_oracle_windows():
         glob, rho_o, u_o = oracle_window_fields(wl, 41, 12, centre)
         er, eu = rel_errors(rho[glob], u[:, glob], rho_o, u_o)
         assert er < TOL and eu < TOL, (centre, er, eu)
+
+
+@pytest.mark.parametrize("soft", [False, True])
+@pytest.mark.parametrize("storage,k", STORAGES, ids=[s for s, _ in STORAGES])
+@pytest.mark.parametrize("lattice,shape", [("D2V9", (301, 251, 1)), ("D2V9", (101, 600, 1)), ("D2V9", (1399, 1300, 1)),
+                                           ("D2V9", (1250, 1001, 1)), ("D2V9", (2, 40001, 1)), ("D2V9", (500, 500, 1)),
+                                           ("D2V9", (768, 100, 1)), ("D3V19", (37, 40, 41)), ("D3V19", (50, 41, 38)),
+                                           ("D3V19", (64, 40, 41))])
+def test_inplace_ragged_rows_bitwise(lattice, shape, storage, k, soft):
+    """Grids without solids from 50000 nodes, on which the local phase runs as one row or by rows:
+    rows that start in mid-line or on lines, odd and even node counts, states within and beyond the L2s."""
+    wl = W.random_fields(lattice, *shape, seed=13, solid_fraction=0.0, soft=soft, umax=0.02)
+    wl.tau, wl.E = 0.7, (2e-4, -1e-4, 0)
+    if wl.s is not None:
+        wl.s = 0.3 * wl.s
+    one, two = (gpu_sim(wl, inplace=i, storage=storage, dev_scale_log2=k) for i in (True, False))
+    for steps in (2, 3):
+        one.step(steps)
+        two.step(steps)
+        assert torch.equal(one.export_f64(), two.export_f64()), steps
