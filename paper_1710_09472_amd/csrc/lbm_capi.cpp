@@ -342,13 +342,14 @@ EvenSlots march3_even(bool f32, bool solids, bool soft, bool slip, bool sr, int 
 struct Route {
     int kernel;  // LBM_LAUNCH_*
     int most;    // steps per launch at most
+    int least;   // and at least, where it takes several
 };
 Route step_route(const lbm_params &p, int N, size_t state_bytes, bool solids, bool soft, bool inplace,
                  const TilePlan &tile, const March3Plan &march3)
 {
-    const Route single{LBM_LAUNCH_SINGLE, 1};
-    if (inplace) return {LBM_LAUNCH_INPLACE, 1};
-    if (p.lattice == LBM_D1V7) return {LBM_LAUNCH_THERMAL, kThermalSteps};
+    const Route single{LBM_LAUNCH_SINGLE, 1, 1};
+    if (inplace) return {LBM_LAUNCH_INPLACE, 1, 1};
+    if (p.lattice == LBM_D1V7) return {LBM_LAUNCH_THERMAL, kThermalSteps, 3};
     if (p.storage == LBM_F32 && solids && state_bytes >= (1ull << 32)) return single;
     const int force = force_level(p);
     if (p.lattice == LBM_D3V19) {
@@ -361,7 +362,7 @@ Route step_route(const lbm_params &p, int N, size_t state_bytes, bool solids, bo
         // 59 x 158 x 61, 3.7 slots, 0.79 - 0.83; 256 x 128 x 16, 3.5 slots, 0.96 - 1.04)
         const float ragged = f32 && p.nx % 16 ? 0.25f : 0.f;
         if (march3.slots > even.at_one + ragged + even.per_lane * (march3.lanes - 1.f)) return single;
-        return {LBM_LAUNCH_MARCH3, 2};
+        return {LBM_LAUNCH_MARCH3, 2, 2};
     }
     // The one exception: states in the Infinity Cache without solids, where stochastic rounding, a
     // source term and a porosity field or magnetic term together bound the single step by the
@@ -377,8 +378,17 @@ Route step_route(const lbm_params &p, int N, size_t state_bytes, bool solids, bo
     // columns 130 / 70 / 119, 100 columns 84 / 76 / 105. (Tiles take 32-bit byte offsets.)
     const bool thin = p.nx < 100 || p.ny <= 8;
     if (thin && state_bytes >= (1ull << 32)) return single;
-    if (thin || N < 8000000) return {LBM_LAUNCH_TILE, tile.steps};
-    return {LBM_LAUNCH_MARCH, kMarchSteps};
+    if (!thin && N >= 8000000) return {LBM_LAUNCH_MARCH, kMarchSteps, 3};
+    // Tiles of which a good part lies outside the grid (73 rows in four tiles of 24) compute that part
+    // too. With 16-bit storage and porosity three steps per launch no longer pay for it, with
+    // stochastic rounding and a field nor do five, unless rows of few columns cost the single step as
+    // much (five / three steps per launch against single ones, 8241 x 73: FP16 0.60 / 0.72, stochastic
+    // 0.71 / 0.78, with porosity 0.99 / 1.11, and E, B 1.13 / 1.21, to nearest with them 1.00 / 1.09;
+    // 1000 x 700 0.46 / 0.53, 0.57 / 0.60, 0.72 / 0.78, 0.86 / 0.89, 0.77 / 0.80; 50 x 8533 with all of
+    // them 0.77 / 0.78; with solids too 8025 x 26 1.09 / 1.16, 8241 x 73 0.98 / 1.06).
+    const bool ragged = p.storage != LBM_F32 && soft && p.nx >= 100 && N >= 200000 && tile.ragged >= 1.15f;
+    if (ragged && p.rounding != LBM_ROUND_NEAREST && force != 0 && tile.ragged >= (solids ? 1.6f : 1.2f)) return single;
+    return {LBM_LAUNCH_TILE, tile.steps, ragged ? 5 : 3};
 }
 Route step_route(const lbm_t h)
 {
@@ -392,7 +402,8 @@ Route step_route(const lbm_t h)
 int launch_steps(const Route &r, int nsteps, int left)
 {
     if (r.kernel == LBM_LAUNCH_MARCH3) return nsteps - left < nsteps / 4 * 4 ? 2 : 1;
-    return std::min(r.most, (left - 1) / 2 * 2 + 1);
+    const int k = std::min(r.most, (left - 1) / 2 * 2 + 1);
+    return k >= r.least ? k : 1;
 }
 // Compute units of the stream's device (NULL: the current one), by which the multi-step launches
 // are planned; without a device the 256 of an MI355X.

@@ -228,6 +228,7 @@ struct TilePlan {
     int steps;     // most steps per launch (odd)
     int tx, ty;    // nodes a block writes
     int ntx, nty;  // tiles along x and y
+    float ragged;  // nodes of the tiles over nodes of the grid
 };
 constexpr int kTileThreads = 1024;  // threads per block at most
 constexpr int kTileSteps = 17;      // steps per launch at most

@@ -48,6 +48,7 @@ TilePlan tile_plan(int nx, int ny, int cus)
     p.ty = std::min(p.ty, ny);
     p.ntx = (nx + p.tx - 1) / p.tx;
     p.nty = (ny + p.ty - 1) / p.ty;
+    p.ragged = (float)((double)p.ntx * p.tx * p.nty * p.ty / ((double)nx * ny));
     return p;
 }
 

@@ -152,3 +152,19 @@ def test_two_step_launches_of_3d_grids_are_planned_by_their_shape():
         assert kernel(*dims, **E) == "k_march3"
     assert kernel(256, 128, 128, True, E=(1e-6, 0, 0), B=(0, 0, 1e-3)) == kernel(128, 128, 128, True, True) == "k_march3"
     assert kernel(128, 256, 256, **bf16) == kernel(128, 256, 256, True, True, **bf16) == "k_march3"
+
+
+def test_ragged_16_bit_tiles_take_launches_that_pay():
+    """Tiles that reach beyond the grid (73 rows in four tiles of 24) take five steps per launch or
+    single ones with 16-bit storage and porosity, and with stochastic rounding and a field single ones."""
+    def plan(nx, ny, steps, porosity=False, **kw):
+        return lbm.launch_plan(lbm.make_params("D2V9", nx, ny, **kw), steps, porosity=porosity)
+
+    sr, E = {"storage": "f16", "rounding": "stochastic"}, {"E": (1e-6, 0, 0)}
+    for args in ((8241, 73, 13, True), (1000, 700, 13, True)):
+        assert plan(*args) == ("k_tile", 5, 3)  # 5 + 5 + 3
+    assert plan(8241, 73, 13, **sr) == plan(1000, 700, 13, True, **sr, **E) == plan(50, 8533, 13, True, **sr, **E) \
+        == ("k_tile", 5, 3)
+    assert plan(8241, 73, 13, True, **sr) == plan(8241, 73, 13, True, storage="bf16", **E) == ("k_tile", 5, 5)
+    assert plan(8241, 73, 13, True, **sr, **E) == ("k_step", 1, 13)
+    assert plan(8241, 73, 3, True, storage="bf16") == ("k_step", 1, 3)
