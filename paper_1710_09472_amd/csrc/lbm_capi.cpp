@@ -306,38 +306,46 @@ const void *links_of(const lbm_t h) { return has_solids(h) ? h->links : nullptr;
 // tiles / strips): FP32 2048^2 19.2 / 22.1, 4096 x 2048 38.9 / 38.9, 4096^2 76.0 / 69.4; with
 // solids 23.2 / 27.4, 46.7 / 47.2, 91.7 / 82.2; FP16 18.1 / 21.8, 36.0 / 36.0, 71.0 / 63.2; FP16
 // with solids, stochastic 28.3 / 31.3, 56.4 / 56.8, 111 / 103.
-// D3V19: blocks marching along z, two steps per launch, where the grid fills them (march3_even; FP32
-// from 0.5 M nodes) and memory bounds the single step: FP32 (128^3 42 - 50 / 59 - 66 us per step with
-// two / one per launch, 256 x 256 x 128 148 - 179 / 232 - 265), 16-bit states with solids beyond the
-// 256 MB Infinity Cache (256 x 256 x 128 158 - 184 / 269 - 280; 128^3 no gain), and 16-bit ones
-// without solids where neither a source term nor stochastic rounding adds to the VALU's work (FP16
-// 128^3 28 - 30 / 32 - 34; with a source 31 - 36 / 33 - 35, stochastic 256 x 256 x 128 124 - 142 /
-// 114 - 120). The reads of bounced links take 32-bit offsets (FP32 with solids: states below 4 GiB).
+// D3V19: blocks marching along z, two steps per launch, where the grid fills them (EvenSlots below;
+// FP32 from 0.5 M nodes) and memory bounds the single step: FP32 (128^3 42 - 50 / 59 - 66 us per step
+// with two / one per launch, 256 x 256 x 128 148 - 179 / 232 - 265), and 16-bit states where neither a
+// source term nor stochastic rounding adds to the VALU's work (FP16 128^3 28 - 30 / 32 - 34; with a
+// source 31 - 36 / 33 - 35, stochastic 256 x 256 x 128 124 - 142 / 114 - 120), or, with solids from
+// 8 M nodes, rows that start in mid-line cost the single step as much. The reads of bounced links
+// take 32-bit offsets (FP32 with solids: states below 4 GiB).
 // k_march3's time is its rounds of blocks times the planes they walk, whatever share of a block's
 // 64 x 13 nodes the grid fills; single steps pay for memory, and on narrow grids for the lanes that a
 // row leaves idle. So the line lies at a number of slots per node (March3Plan), higher where the
-// single step wastes lanes too. Ratios of the times, two / one per launch, FP32: 128^3 (1.75 slots)
-// 0.72 without solids, 0.77 with, 0.77 with porosity as well and E, 0.90 without a field (those
-// instances spill); 96^3 (2.67) 0.73, 0.84, 0.87, 1.04; 256 x 128 x 16 (3.5) 0.94, 1.03, 1.04, 1.30;
-// 4096 x 2048 x 1 (5.0) 1.07, 1.25, -, 1.66; 32 x 128 x 128 (4.5, two lanes per node) 0.93, 1.03,
-// 1.10, 1.22; 24 x 160 x 160 (5.1, 2.7 lanes) 0.66, 0.77, -, 0.88. 16 bits from HBM, without solids
-// 128 x 256 x 256 (1.44) 0.81 - 0.96, 512 x 512 x 32 (1.72) 1.01 - 1.12, 96 x 300 x 300 (1.9, 1.3
-// lanes) 0.79 - 0.91; from the cache 128^3 0.83 - 0.94; with solids 2048^2 x 2 (3.1) 0.77 - 0.86,
-// 4096 x 2048 x 1 1.05; with porosity 256 x 16 x 2048 (2.1) 0.85 - 0.96, stochastic 1.04; with
-// free-slip planes 2048 x 1024 x 4 (2.2) 1.03, with porosity 1.40.
+// single step wastes lanes too, or starts rows in mid-line. Ratios of the times, two / one per launch.
+// FP32: 128^3 (1.75 slots) 0.72 without solids, 0.77 with, 0.77 with porosity as well and E, 0.90
+// without a field (those instances spill); 96^3 (2.67) 0.73, 0.84, 0.87, 1.04; 256 x 128 x 16 (3.5)
+// 0.94, 1.03, 1.04, 1.30; 4096 x 2048 x 1 (5.0) 1.07, 1.25, -, 1.66; 32 x 128 x 128 (4.5, two lanes per
+// node) 0.93, 1.03, 1.10, 1.22; 24 x 160 x 160 (5.1, 2.7 lanes) 0.66, 0.77, -, 0.88; with free-slip
+// planes 96^3 0.93, 208 x 16 x 858 (2.75) 1.06, with porosity 256 x 32 x 256 (2.0) 0.83, with E and B
+// too 1.12, 256 x 128 x 128 (1.56) 1.09.
+// 16 bits without solids: 128 x 256 x 256 (1.44) 0.81 - 0.96, 512 x 512 x 32 (1.72) 1.01 - 1.12,
+// 96 x 300 x 300 (1.9, 1.3 lanes) 0.79 - 0.91; from the Infinity Cache 128^3 0.83 - 0.94. 16 bits with
+// solids, from walls to dense scattered obstacles: rows in mid-line 229 x 181 x 388 (1.53) 0.61 - 1.01,
+// 200 x 200 x 210 (1.75) 0.64 - 1.23, 229 x 181 x 388 with free-slip planes and porosity up to 1.17;
+// rows on lines 256 x 256 x 128 (1.44) nearest without porosity or a source 0.57 - 0.99, with any of
+// them 0.6 - 1.33: there the single step wins but for dense obstacles.
 struct EvenSlots {
     float at_one, per_lane;  // slots up to which two steps per launch are faster, at one lane per node, and per lane more
 };
-EvenSlots march3_even(bool f32, bool solids, bool soft, bool slip, bool sr, int force, bool cached)
+EvenSlots march3_even_f32(bool solids, bool soft, bool slip, int force)
 {
-    if (f32 && !solids) return soft ? EvenSlots{3.45f, 0.62f} : EvenSlots{4.1f, 0.65f};
-    if (f32 && !soft) return {3.45f, 1.f};
-    if (f32 && !slip && force == 1) return {3.3f, 0.65f};
-    if (f32 && !slip && force == 2) return {2.5f, 0.65f};
-    if (f32) return {2.f, 0.75f};
-    if (!solids) return {cached ? 1.8f : 1.5f, 1.25f};
-    if (slip) return {soft ? 1.7f : 2.1f, 0.4f};
-    return {!soft ? 3.2f : sr ? 2.f : 2.3f, 0.4f};
+    if (!solids) return soft ? EvenSlots{3.45f, 0.62f} : EvenSlots{4.1f, 0.65f};
+    if (!soft) return slip ? EvenSlots{2.5f, 0.8f} : EvenSlots{3.45f, 1.f};
+    if (slip) return {force == 2 ? 1.5f : 2.f, 0.75f};
+    if (force == 1 || force == 2) return {force == 1 ? 3.3f : 2.5f, 0.65f};
+    return {2.f, 0.75f};
+}
+// plain: rounded to nearest, without a source term; cached: both states in the Infinity Cache
+EvenSlots march3_even_16(bool solids, bool soft, bool slip, bool plain, bool cached, bool mid_line)
+{
+    if (!solids) return {plain ? cached ? 1.8f : 1.5f : 0.f, plain ? 1.25f : 0.f};
+    if (mid_line) return slip && soft ? EvenSlots{1.45f, 0.3f} : EvenSlots{1.5f, 0.6f};
+    return {plain && !soft && !slip ? 1.45f : 0.f, 0.f};
 }
 struct Route {
     int kernel;  // LBM_LAUNCH_*
@@ -353,14 +361,16 @@ Route step_route(const lbm_params &p, int N, size_t state_bytes, bool solids, bo
     if (p.storage == LBM_F32 && solids && state_bytes >= (1ull << 32)) return single;
     const int force = force_level(p);
     if (p.lattice == LBM_D3V19) {
-        const bool f32 = p.storage == LBM_F32, sr = p.rounding != LBM_ROUND_NEAREST;
-        const bool plain = !sr && (force == 0 || force == 3);  // 16 bits, without solids
-        if (N < (f32 ? 500000 : solids ? 8000000 : 2000000) || !(f32 || solids || plain)) return single;
-        const bool cached = 2 * state_bytes <= (256ull << 20);  // both states in the Infinity Cache
-        const EvenSlots even = march3_even(f32, solids, soft, p.slip != 0, sr, force, cached);
+        const bool f32 = p.storage == LBM_F32, slip = p.slip != 0;
+        if (N < (f32 ? 500000 : solids ? 8000000 : 2000000)) return single;
+        const bool plain = p.rounding == LBM_ROUND_NEAREST && (force == 0 || force == 3);
+        const EvenSlots even = f32 ? march3_even_f32(solids, soft, slip, force)
+                                   : march3_even_16(solids, soft, slip, plain, 2 * state_bytes <= (256ull << 20),
+                                                    p.nx % 64 != 0);
         // FP32 rows that start within a 64-byte line cost the single step more (with solids
-        // 59 x 158 x 61, 3.7 slots, 0.79 - 0.83; 256 x 128 x 16, 3.5 slots, 0.96 - 1.04)
-        const float ragged = f32 && p.nx % 16 ? 0.25f : 0.f;
+        // 59 x 158 x 61, 3.7 slots, 0.79 - 0.83; 256 x 128 x 16, 3.5 slots, 0.96 - 1.04; with free-slip
+        // planes 105 x 114 x 57, 3.1 slots, 0.72 - 0.88)
+        const float ragged = !f32 || p.nx % 16 == 0 ? 0.f : slip && !soft ? 0.8f : 0.25f;
         if (march3.slots > even.at_one + ragged + even.per_lane * (march3.lanes - 1.f)) return single;
         return {LBM_LAUNCH_MARCH3, 2, 2};
     }

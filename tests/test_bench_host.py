@@ -147,11 +147,17 @@ def test_two_step_launches_of_3d_grids_are_planned_by_their_shape():
     assert kernel(256, 16, 2048, True, True, **E) == kernel(96, 96, 96, True, True, **E) == "k_march3"
     for dims in ((1024, 1024, 8), (512, 512, 32), (256, 16, 2048), (32, 512, 512)):
         assert kernel(*dims, **bf16) == "k_step"
-    assert kernel(2048, 1024, 4, True, True, slip=lbm.SLIP_Y, **bf16) == "k_step"
+    # 16 bits with solids: walls and ordinary obstacles leave the single step ahead where rows lie on lines
+    walls = dict(solids=True, E=(1e-6, 0, 0), **bf16)
+    assert kernel(256, 256, 128, **walls) == kernel(512, 26, 640, **walls) == kernel(200, 200, 210, **walls) == "k_step"
+    assert kernel(128, 256, 256, slip=3, **bf16) == kernel(229, 181, 388, porosity=True, slip=3, **bf16) == "k_step"
+    assert kernel(229, 181, 388, **walls) == kernel(63, 360, 368, porosity=True, **walls) == "k_march3"
+    assert kernel(208, 16, 858, slip=1) == kernel(256, 32, 256, porosity=True, slip=3, B=(0, 0, 1e-3)) == "k_step"
+    assert kernel(256, 32, 256, porosity=True, slip=3) == kernel(96, 96, 96, slip=3, **E) == "k_march3"
     for dims in ((128, 128, 128), (256, 128, 128), (96, 96, 96), (65, 128, 128), (24, 160, 160)):
         assert kernel(*dims, **E) == "k_march3"
     assert kernel(256, 128, 128, True, E=(1e-6, 0, 0), B=(0, 0, 1e-3)) == kernel(128, 128, 128, True, True) == "k_march3"
-    assert kernel(128, 256, 256, **bf16) == kernel(128, 256, 256, True, True, **bf16) == "k_march3"
+    assert kernel(128, 256, 256, **bf16) == kernel(128, 256, 256, True, **bf16) == "k_march3"
 
 
 def test_ragged_16_bit_tiles_take_launches_that_pay():

@@ -50,7 +50,7 @@ def test_2d_instances(kernel, dims, solids, slip, soft, force, storage, rounding
 @pytest.mark.parametrize("force", list(FORCES))
 @pytest.mark.parametrize("soft", [False, True])
 @pytest.mark.parametrize("solids,slip", [(False, 0), (True, 0), (False, 3), (True, 3)])
-@pytest.mark.parametrize("dims", [(63, 105, 196), (125, 92, 151)])
+@pytest.mark.parametrize("dims", [(63, 183, 200), (127, 209, 151)])
 def test_3d_instances_f32(dims, solids, slip, soft, force):
     _same_bits("k_march3", 8, "D3V19", dims, "f32", "nearest", solids, soft, force, slip)
 
