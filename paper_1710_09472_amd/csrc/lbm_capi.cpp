@@ -395,9 +395,11 @@ Route step_route(const lbm_params &p, int N, size_t state_bytes, bool solids, bo
     // much (five / three steps per launch against single ones, 8241 x 73: FP16 0.60 / 0.72, stochastic
     // 0.71 / 0.78, with porosity 0.99 / 1.11, and E, B 1.13 / 1.21, to nearest with them 1.00 / 1.09;
     // 1000 x 700 0.46 / 0.53, 0.57 / 0.60, 0.72 / 0.78, 0.86 / 0.89, 0.77 / 0.80; 50 x 8533 with all of
-    // them 0.77 / 0.78; with solids too 8025 x 26 1.09 / 1.16, 8241 x 73 0.98 / 1.06).
-    const bool ragged = p.storage != LBM_F32 && soft && p.nx >= 100 && N >= 200000 && tile.ragged >= 1.15f;
-    if (ragged && p.rounding != LBM_ROUND_NEAREST && force != 0 && tile.ragged >= (solids ? 1.6f : 1.2f)) return single;
+    // them 0.77 / 0.78; with solids too 8025 x 26 1.09 / 1.16, 8241 x 73 0.98 / 1.06; to nearest with
+    // walls 8975 x 29 1.04).
+    const bool ragged = p.storage != LBM_F32 && soft && p.nx >= 100 && N >= 150000 && tile.ragged >= 1.15f;
+    const float most_ragged = solids || p.rounding == LBM_ROUND_NEAREST ? 1.6f : 1.2f;
+    if (ragged && force != 0 && tile.ragged >= most_ragged) return single;
     return {LBM_LAUNCH_TILE, tile.steps, ragged ? 5 : 3};
 }
 Route step_route(const lbm_t h)

@@ -174,3 +174,4 @@ def test_ragged_16_bit_tiles_take_launches_that_pay():
     assert plan(8241, 73, 13, True, **sr) == plan(8241, 73, 13, True, storage="bf16", **E) == ("k_tile", 5, 5)
     assert plan(8241, 73, 13, True, **sr, **E) == ("k_step", 1, 13)
     assert plan(8241, 73, 3, True, storage="bf16") == ("k_step", 1, 3)
+    assert plan(8975, 29, 13, True, storage="f16", **E) == ("k_step", 1, 13)
