@@ -300,10 +300,9 @@ int force_level(const lbm_params &p)
 // link masks exist where there are solids: obstacles of the mask, or slip wall planes
 bool has_solids(const lbm_t h) { return h->mask != nullptr || h->p.slip != 0; }
 const void *links_of(const lbm_t h) { return has_solids(h) ? h->links : nullptr; }
-// How several steps go into one launch, on two state buffers. D2V9: tiles on small grids, whose
-// single step is a launch and little else, up to the size where strips in registers, which
-// recompute less, measured the same in every format, with solids and without (us per step,
-// tiles / strips): FP32 2048^2 19.2 / 22.1, 4096 x 2048 38.9 / 38.9, 4096^2 76.0 / 69.4; with
+// How several steps go into one launch, on two state buffers. D2V9: tiles up to the size where strips
+// in registers, which recompute less, measured the same in every format, with solids and without
+// (and on thin grids at any size, below; us per step, tiles / strips): FP32 2048^2 19.2 / 22.1, 4096 x 2048 38.9 / 38.9, 4096^2 76.0 / 69.4; with
 // solids 23.2 / 27.4, 46.7 / 47.2, 91.7 / 82.2; FP16 18.1 / 21.8, 36.0 / 36.0, 71.0 / 63.2; FP16
 // with solids, stochastic 28.3 / 31.3, 56.4 / 56.8, 111 / 103.
 // D3V19: blocks marching along z, two steps per launch, where the grid fills them (EvenSlots below;

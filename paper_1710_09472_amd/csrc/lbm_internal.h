@@ -223,7 +223,7 @@ hipError_t launch_march3_f16_sr(int force, const StepArgs &a, const March3Plan &
 hipError_t launch_march3_bf16(int force, const StepArgs &a, const March3Plan &p, const uint32_t *keys, hipStream_t st);
 hipError_t launch_march3_bf16_sr(int force, const StepArgs &a, const March3Plan &p, const uint32_t *keys,
                                  hipStream_t st);
-// The same on small grids by tiles (lbm_tile.hip): 1 .. p.steps steps in one launch.
+// The same by tiles (lbm_tile.hip), an odd number of steps from 1 to p.steps in one launch.
 struct TilePlan {
     int steps;     // most steps per launch (odd)
     int tx, ty;    // nodes a block writes

@@ -13,8 +13,9 @@
 // Node arithmetic, rounding of 16-bit storage between the steps and bits are those of single
 // steps. Between the steps bounced populations come from the node's own registers.
 // What bounds it: memory and the VALU in turn, held together by the barrier (FP32 duct
-// 256 x 128 x 128: 743 MB and 55 % VALU issue in 175 us per launch; the column's outer rows,
-// one in 6.5, and two planes per segment are computed twice). Measured on MI355X, us per
+// 256 x 128 x 128: 726 MB and 46 % VALU issue in 172 us per launch; the column's outer rows,
+// one in 6.5, and two planes per segment are computed twice). One block of 16 waves per CU is what
+// its registers allow (100 - 128 VGPRs: four waves per SIMD), whatever its LDS. Measured on MI355X, us per
 // step against single steps, FP32: Hall duct 87 (109), periodic 256^3 300 (480), 128^3
 // porous 43.7 (60.8), 300 x 200 x 100 with obstacles 162 (304); FP16 periodic 256^3 191
 // (239). Two blocks of 7 rows per CU instead of one of 15 measured 10 - 20 % slower (a third

@@ -18,7 +18,7 @@
 // keeps its own convention (kSolidSlotBB).
 //
 // What bounds it: the VALU at five steps per launch (about 500 instructions per row of 64
-// lanes, of which 56 are written; FP32 4096^2 issues VALU 70 % of the time), no longer memory:
+// lanes, of which 56 are written; FP32 4096^2 issues VALU in 89 % of its cycles), no longer memory:
 // on that grid a launch of two steps took 320 us, of three 330 us, of five 350 us, against
 // 190 us for one single step. Measured on MI355X, us per step against single steps: periodic
 // 4096^2 FP32 70 (190), FP16 63 (101); with disks FP32 82, FP16 86. Two nodes per lane (fewer lanes lost

@@ -1,4 +1,4 @@
-// lbm_tile.hip -- several steps per launch on small D2V9 grids (lbm_tile_kernels.h): FP32 instances, the
+// lbm_tile.hip -- several steps per launch on tiles of D2V9 grids (lbm_tile_kernels.h): FP32 instances, the
 // choice of tiles and the dispatch over storage formats.
 #include "lbm_tile_kernels.h"
 

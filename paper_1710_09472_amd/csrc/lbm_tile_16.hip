@@ -1,4 +1,4 @@
-// lbm_tile_16.hip -- several steps per launch on small D2V9 grids (lbm_tile_kernels.h): 16-bit storage rounded
+// lbm_tile_16.hip -- several steps per launch on tiles of D2V9 grids (lbm_tile_kernels.h): 16-bit storage rounded
 // to nearest.
 #include "lbm_tile_kernels.h"
 

@@ -1,8 +1,8 @@
-// lbm_tile_kernels.h -- several time steps of the two-buffer D2V9 scheme in one launch, for
-// grids whose single step is bound by its launch.
+// lbm_tile_kernels.h -- several time steps of the two-buffer D2V9 scheme in one launch on tiles of
+// the grid: grids below 8 M nodes, and beyond it those of few rows or columns.
 //
 // A step of a small grid takes 3 - 4 us whatever its size (a launch on an idle GPU, a round
-// trip to memory and back). k_tile takes `steps` steps per launch on tiles of the grid: a
+// trip to memory and back); a step of a larger one is bound by its pass over memory. k_tile takes `steps` steps per launch on tiles of the grid: a
 // block owns one node per thread of a tile and a halo of steps - 1 nodes around it (none
 // along an axis that the tile spans as a whole: there it wraps inside the block). Step 1
 // pulls from memory as the single step does; between the steps the post-collision

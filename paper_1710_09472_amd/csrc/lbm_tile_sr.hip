@@ -1,4 +1,4 @@
-// lbm_tile_sr.hip -- several steps per launch on small D2V9 grids (lbm_tile_kernels.h): 16-bit storage with
+// lbm_tile_sr.hip -- several steps per launch on tiles of D2V9 grids (lbm_tile_kernels.h): 16-bit storage with
 // stochastic rounding.
 #include "lbm_tile_kernels.h"
 
