@@ -302,9 +302,10 @@ bool has_solids(const lbm_t h) { return h->mask != nullptr || h->p.slip != 0; }
 const void *links_of(const lbm_t h) { return has_solids(h) ? h->links : nullptr; }
 // How several steps go into one launch, on two state buffers. D2V9: tiles up to the size where strips
 // in registers, which recompute less, measured the same in every format, with solids and without
-// (and on thin grids at any size, below; us per step, tiles / strips): FP32 2048^2 19.2 / 22.1, 4096 x 2048 38.9 / 38.9, 4096^2 76.0 / 69.4; with
-// solids 23.2 / 27.4, 46.7 / 47.2, 91.7 / 82.2; FP16 18.1 / 21.8, 36.0 / 36.0, 71.0 / 63.2; FP16
-// with solids, stochastic 28.3 / 31.3, 56.4 / 56.8, 111 / 103.
+// (and on thin grids at any size, below). us per step, tiles / strips: FP32 2048^2 19.2 / 22.1,
+// 4096 x 2048 38.9 / 38.9, 4096^2 76.0 / 69.4; with solids 23.2 / 27.4, 46.7 / 47.2, 91.7 / 82.2;
+// FP16 18.1 / 21.8, 36.0 / 36.0, 71.0 / 63.2; with solids, stochastic 28.3 / 31.3, 56.4 / 56.8,
+// 111 / 103.
 // D3V19: blocks marching along z, two steps per launch, where the grid fills them (EvenSlots below;
 // FP32 from 0.5 M nodes) and memory bounds the single step: FP32 (128^3 42 - 50 / 59 - 66 us per step
 // with two / one per launch, 256 x 256 x 128 148 - 179 / 232 - 265), and 16-bit states where neither a
@@ -373,10 +374,11 @@ Route step_route(const lbm_params &p, int N, size_t state_bytes, bool solids, bo
         if (march3.slots > even.at_one + ragged + even.per_lane * (march3.lanes - 1.f)) return single;
         return {LBM_LAUNCH_MARCH3, 2, 2};
     }
-    // The one exception: states in the Infinity Cache without solids, where stochastic rounding, a
-    // source term and a porosity field or magnetic term together bound the single step by the
-    // VALU too, and tiles repeat that work in their halos (FP16 2048^2 tiles / single steps with E
-    // and B 31.9 / 30.5, with E and porosity 33.3 / 31.7, both 35.9 / 32.2).
+    // One exception: states in the Infinity Cache without solids, where stochastic rounding, a source
+    // term and a porosity field or magnetic term together bound the single step by the VALU too, and
+    // tiles repeat that work in their halos: about even, and slower where all come together (2048^2
+    // tiles / single steps, E and B 28.6 / 30.3 in FP16 and 27.2 / 30.2 in BF16, E and porosity
+    // 32.8 / 32.1 and 30.8 / 31.8, all three 35.4 / 31.8 and 32.6 / 32.2).
     if (p.rounding != LBM_ROUND_NEAREST && !solids && (force == 2 || (force == 1 && soft)) && N >= 2000000 &&
         N < 6000000)
         return single;
